@@ -193,6 +193,7 @@ hipError_t launch_swarm_init(const SwarmDev<P>& w, hipStream_t s);
 template <class P>
 hipError_t launch_swarm_step(const SwarmDev<P>& w, uint32_t step0, int n_steps, int accumulate,
                              hipStream_t s);
+int swarm_launch_steps(int64_t ions);
 template <class P>
 hipError_t launch_swarm_reduce(const SwarmDev<P>& w, hipStream_t s);
 template <class P>

@@ -2264,9 +2264,9 @@ struct SwarmImpl : SwarmBase {
   int run(int64_t n, int accumulate) override {
     if (n < 0) return fail(HD_EINVAL, "n_steps must be non-negative");
     HD_TRY(hipSetDevice(device));
-    constexpr int64_t kChunk = 256;  // steps per launch
-    for (int64_t done = 0; done < n; done += kChunk) {
-      const int k = (int)std::min<int64_t>(kChunk, n - done);
+    const int64_t chunk = swarm_launch_steps((int64_t)p.n_fields * p.n_ions);
+    for (int64_t done = 0; done < n; done += chunk) {
+      const int k = (int)std::min<int64_t>(chunk, n - done);
       HD_TRY(launch_swarm_step<P>(w, (uint32_t)(step + done), k, accumulate ? 1 : 0, stream));
     }
     step += n;
@@ -2381,12 +2381,12 @@ int swarm_noalloc(const hd_swarm_params& p, int64_t n_relax, int64_t n_avg, hipS
   // start at zero, velocities and ion sums are set by the load
   HD_TRY(launch_swarm_clear<P>(w, stream));
   HD_TRY(launch_swarm_init<P>(w, stream));
-  constexpr int64_t kChunk = 256;  // steps per launch, as hd_swarm_run
+  const int64_t chunk = swarm_launch_steps((int64_t)n);
   int64_t step = 0;
   for (int acc_on = 0; acc_on < 2; ++acc_on) {
     const int64_t m = acc_on ? n_avg : n_relax;
-    for (int64_t done = 0; done < m; done += kChunk) {
-      const int k = (int)std::min<int64_t>(kChunk, m - done);
+    for (int64_t done = 0; done < m; done += chunk) {
+      const int k = (int)std::min<int64_t>(chunk, m - done);
       HD_TRY(launch_swarm_step<P>(w, (uint32_t)(step + done), k, acc_on, stream));
     }
     step += m;

@@ -50,6 +50,24 @@ def test_swarm_matches_oracle(precision):
     _compare(dev, orc, 3)
 
 
+@pytest.mark.parametrize("precision,fields,n_ions,steps", [
+    (0, 1, 1, 40),        # one lane of one wave
+    (1, 2, 65, 40),       # one ion past a wave
+    (0, 1, 524289, 5),    # one ion past the device's lanes: waves hand out further ions
+    (1, 2, 140001, 5),    # the same in FP64, two swarms, ragged last wave
+    (0, 300, 257, 3),     # many swarms
+    (1, 1, 700, 1030),    # across the launch boundary of a small swarm
+])
+def test_ions_per_wave(precision, fields, n_ions, steps):
+    p = W.swarm_params(np.linspace(1e5, 8e6, fields), n_ions=n_ions, precision=precision)
+    dev, orc = hd.Swarm(p), oracle.Swarm(p, contract=True)
+    dev.run(steps)
+    orc.run(steps)
+    dev.run(steps, accumulate=True)
+    orc.run(steps, accumulate=True)
+    _compare(dev, orc, fields)
+
+
 def test_table_overflow_matches():
     # a table ending at 0.16 eV: many candidates fall beyond it
     p = W.swarm_params([3e6], n_ions=1000, precision=0,
