@@ -156,6 +156,14 @@ struct Disch {
   uint64_t grid_bytes;
 };
 
+// Parts of a read-out (k_readout) and their offsets in its buffer, in 8-byte
+// words; off[kRoParts] is its length.
+enum { kRoState, kRoCnt, kRoNi, kRoGam, kRoPhi, kRoE, kRoAccCnt, kRoAccNi, kRoEedf, kRoParts };
+struct Readout {
+  uint32_t off[kRoParts + 1];
+};
+static_assert(sizeof(State) % 8 == 0, "read out in 8-byte words");
+
 // Auxiliary ion swarm: n_fields independent swarms of n_ions ions, ion i of
 // swarm f at index f * n_ions + i of every array.
 constexpr int kSwarmThreads = 256;
@@ -186,6 +194,9 @@ namespace hd {
 template <class P>
 hipError_t launch_finalize(const Disch<P>* d_dev, int D, int field_only, int nn_max,
                            int app_blocks, hipStream_t s);
+template <class P>
+hipError_t launch_readout(const Disch<P>* d, const Readout& r, uint32_t want, uint64_t* out,
+                          hipStream_t s);
 template <class P>
 hipError_t launch_diag(int64_t n, const P* a, const P* b, P* out, hipStream_t s);
 template <class P>

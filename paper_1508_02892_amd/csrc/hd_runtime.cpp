@@ -625,6 +625,43 @@ struct DevMem {
   }
 };
 
+// Pinned host memory of a handle that read-outs are written to.
+struct HostBuf {
+  uint64_t* p = nullptr;
+  int reserve(size_t words) {
+    if (hipHostMalloc((void**)&p, words * 8, hipHostMallocDefault) != hipSuccess) {
+      p = nullptr;
+      return fail(HD_ENOMEM, "pinned host memory for read-outs");
+    }
+    return HD_OK;
+  }
+  ~HostBuf() {
+    if (p) (void)hipHostFree(p);
+  }
+};
+
+// Layout of a discharge's read-out: nn nodes, S ion species, nb1 EEDF entries.
+Readout readout_layout(size_t nn, size_t S, size_t nb1) {
+  const size_t words[kRoParts] = {sizeof(State) / 8, nn, S * nn, S * nn, nn, nn, nn, nn, nb1};
+  Readout r;
+  r.off[0] = 0;
+  for (int k = 0; k < kRoParts; ++k) r.off[k + 1] = r.off[k] + (uint32_t)words[k];
+  return r;
+}
+
+// The parts that the non-null arrays of m need.
+uint32_t readout_parts(const hd_moment_set& m) {
+  uint32_t w = 1u << kRoState | 1u << kRoCnt;  // the live count is the deposit's total
+  if (m.n_i || m.n_species) w |= 1u << kRoNi;
+  if (m.gamma_i || m.gamma_species) w |= 1u << kRoGam;
+  if (m.phi) w |= 1u << kRoPhi;
+  if (m.E) w |= 1u << kRoE;
+  if (m.n_e_avg) w |= 1u << kRoAccCnt;
+  if (m.n_i_avg) w |= 1u << kRoAccNi;
+  if (m.eedf_counts || m.eedf) w |= 1u << kRoEedf;
+  return w;
+}
+
 // ---------------------------------------------------------------------------
 // Batch of discharges advanced together.
 // ---------------------------------------------------------------------------
@@ -673,6 +710,7 @@ struct Batch : BatchBase {
   Disch<P>* d_desc = nullptr;
 
   DevMem mem;
+  HostBuf host;  // read-outs of one discharge (the largest)
 
   ~Batch() override { drop_graphs(); }
 
@@ -897,6 +935,9 @@ struct Batch : BatchBase {
     if (int rc = mem.get(sizeof(Disch<P>) * D, (void**)&d_desc, "the discharge descriptors"))
       return rc;
     HD_TRY(upload_desc());
+    size_t words = 0;
+    for (const auto& h : hs) words = std::max(words, (size_t)readout_of(h).off[kRoParts]);
+    if (int rc = host.reserve(words)) return rc;
     HD_TRY(launch_finalize<P>(d_desc, D, 1, nn_max, 0, stream));
     HD_TRY(hipStreamSynchronize(stream));
     for (int i = 0; i < D; ++i) {  // the field of step 0 must be finite
@@ -1064,6 +1105,12 @@ struct Batch : BatchBase {
   int sync_state(int i, State& st) {
     HD_TRY(hipStreamSynchronize(stream));
     HD_TRY(hipMemcpy(&st, hs[i].dd.st, sizeof(State), hipMemcpyDeviceToHost));
+    return state_error(st);
+  }
+
+  // The error that a state of the idle stream holds, if any; a capacity
+  // overflow that can be is rolled back first (st is then the state after).
+  int state_error(State& st) {
     if (st.error == HD_ECAPACITY && D == 1 && st.ckpt_valid && st.ckpt_step <= st.error_step)
       return rollback(st);
     if (st.error) {
@@ -1296,19 +1343,36 @@ struct Batch : BatchBase {
 
   int moments(int i, hd_moment_set* m) {
     if (i < 0 || i >= D || !m) return fail(HD_EINVAL, "bad index or output");
-    State st;
-    const int rc = sync_state(i, st);
-    const int rc2 = fill_moments(hs[i], st, m);
+    const Readout r = readout_of(hs[i]);
+    HD_TRY(read_out(d_desc + i, r, *m, host.p, stream));
+    State st = *reinterpret_cast<const State*>(host.p);
+    const int rc = state_error(st);
+    // after a roll-back, the state that it left
+    if (rc && read_out(d_desc + i, r, *m, host.p, stream) != hipSuccess) return rc;
+    fill_moments(hs[i], r, host.p, m);
     m->graph_steps = graph_steps;
     m->rollbacks = rollbacks;
-    return rc ? rc : rc2;
+    return rc;
   }
 
-  // Moments of a discharge whose stream is idle, given its State.
-  static int fill_moments(const Host<P>& h, const State& st, hd_moment_set* m) {
+  static Readout readout_of(const Host<P>& h) {
+    return readout_layout((size_t)h.dd.nn, (size_t)h.dd.S, (size_t)h.dd.nbins + 1);
+  }
+  // Waits for the stream's work and brings what m asks for to buf.
+  static hipError_t read_out(const Disch<P>* d, const Readout& r, const hd_moment_set& m,
+                             uint64_t* buf, hipStream_t stream) {
+    const hipError_t e = launch_readout<P>(d, r, readout_parts(m), buf, stream);
+    return e == hipSuccess ? hipStreamSynchronize(stream) : e;
+  }
+
+  // Moments of a discharge from its read-out.
+  static void fill_moments(const Host<P>& h, const Readout& r, const uint64_t* buf,
+                           hd_moment_set* m) {
     const Disch<P>& d = h.dd;
-    const int rc = HD_OK;
     const int nn = d.nn;
+    const State& st = *reinterpret_cast<const State*>(buf);
+    auto whole = [&](int part) { return reinterpret_cast<const int64_t*>(buf + r.off[part]); };
+    auto real = [&](int part) { return reinterpret_cast<const double*>(buf + r.off[part]); };
     m->step = st.step;
     m->n_slots = st.n_main;
     m->n_nodes = nn;
@@ -1330,56 +1394,45 @@ struct Batch : BatchBase {
     m->rf_periods = st.rf_periods;
     m->graph_steps = 0;
     m->rollbacks = 0;
-    std::vector<int64_t> cnt(nn);
-    HD_TRY(hipMemcpy(cnt.data(), d.cnt[st.cbuf], nn * 8, hipMemcpyDeviceToHost));
+    const int64_t* cnt = whole(kRoCnt);
     int64_t tot = 0;
     for (int j = 0; j < nn; ++j) tot += cnt[j];
     m->n_live = tot >> 32;
     auto sc = [&](int j) { return (j == 0 || j == d.nc) ? h.scale_wall : h.scale_in; };
-    if (m->cnt) std::copy(cnt.begin(), cnt.end(), m->cnt);
+    if (m->cnt) std::copy(cnt, cnt + nn, m->cnt);
     if (m->n_e)
       for (int j = 0; j < nn; ++j) m->n_e[j] = (double)cnt[j] * sc(j);
     // ion charge density and flux: species 0 alone, or sum_s Z_s x_s
     const int S = d.S;
-    auto net = [&](const double* src, double* out) -> int {
-      std::vector<double> a((size_t)S * nn);
-      HD_TRY(hipMemcpy(a.data(), src, a.size() * 8, hipMemcpyDeviceToHost));
+    auto net = [&](const double* a, double* out) {
+      if (S == 1) {
+        std::copy(a, a + nn, out);
+        return;
+      }
       for (int j = 0; j < nn; ++j) {
         double v = (double)d.Z[0] * a[j];
         for (int q = 1; q < S; ++q) v = v + (double)d.Z[q] * a[(size_t)q * nn + j];
         out[j] = v;
       }
-      return HD_OK;
     };
-    if (m->n_i) {
-      if (S == 1) HD_TRY(hipMemcpy(m->n_i, d.ni, nn * 8, hipMemcpyDeviceToHost));
-      else if (int r = net(d.ni, m->n_i)) return r;
-    }
-    if (m->gamma_i) {
-      if (S == 1) HD_TRY(hipMemcpy(m->gamma_i, d.gam, nn * 8, hipMemcpyDeviceToHost));
-      else if (int r = net(d.gam, m->gamma_i)) return r;
-    }
-    if (m->n_species)
-      HD_TRY(hipMemcpy(m->n_species, d.ni, (size_t)S * nn * 8, hipMemcpyDeviceToHost));
-    if (m->gamma_species)
-      HD_TRY(hipMemcpy(m->gamma_species, d.gam, (size_t)S * nn * 8, hipMemcpyDeviceToHost));
-    if (m->phi) HD_TRY(hipMemcpy(m->phi, d.phi, nn * 8, hipMemcpyDeviceToHost));
-    if (m->E) HD_TRY(hipMemcpy(m->E, d.E, nn * 8, hipMemcpyDeviceToHost));
+    if (m->n_i) net(real(kRoNi), m->n_i);
+    if (m->gamma_i) net(real(kRoGam), m->gamma_i);
+    if (m->n_species) std::copy(real(kRoNi), real(kRoNi) + (size_t)S * nn, m->n_species);
+    if (m->gamma_species) std::copy(real(kRoGam), real(kRoGam) + (size_t)S * nn, m->gamma_species);
+    if (m->phi) std::copy(real(kRoPhi), real(kRoPhi) + nn, m->phi);
+    if (m->E) std::copy(real(kRoE), real(kRoE) + nn, m->E);
     if (m->n_e_avg) {
-      std::vector<uint64_t> a(nn);
-      HD_TRY(hipMemcpy(a.data(), d.acc_cnt, nn * 8, hipMemcpyDeviceToHost));
+      const uint64_t* a = buf + r.off[kRoAccCnt];
       for (int j = 0; j < nn; ++j)
         m->n_e_avg[j] = st.n_acc ? (double)a[j] * sc(j) / (double)st.n_acc : 0.0;
     }
     if (m->n_i_avg) {
-      std::vector<double> a(nn);
-      HD_TRY(hipMemcpy(a.data(), d.acc_ni, nn * 8, hipMemcpyDeviceToHost));
+      const double* a = real(kRoAccNi);
       for (int j = 0; j < nn; ++j) m->n_i_avg[j] = st.n_acc ? a[j] / (double)st.n_acc : 0.0;
     }
     if (m->eedf_counts || m->eedf) {
-      std::vector<uint64_t> e(d.nbins + 1);
-      HD_TRY(hipMemcpy(e.data(), d.eedf, e.size() * 8, hipMemcpyDeviceToHost));
-      if (m->eedf_counts) std::copy(e.begin(), e.end(), m->eedf_counts);
+      const uint64_t* e = buf + r.off[kRoEedf];
+      if (m->eedf_counts) std::copy(e, e + d.nbins + 1, m->eedf_counts);
       if (m->eedf) {
         uint64_t in = 0;
         for (int b = 0; b < d.nbins; ++b) in += e[b];
@@ -1387,7 +1440,6 @@ struct Batch : BatchBase {
         for (int b = 0; b < d.nbins; ++b) m->eedf[b] = in ? (double)e[b] / ((double)in * de) : 0.0;
       }
     }
-    return rc;
   }
 
   int particles(int i, int32_t* cell, void* off, void* vx, void* vy, void* vz, uint32_t* id,
@@ -1675,6 +1727,7 @@ struct Server : ServerBase {
   Disch<P>* d_desc = nullptr;
   State* d_idle = nullptr;
   DevMem mem;  // the admitted jobs' blocks (hipMalloc; released when a job retires)
+  HostBuf host;  // the read-out of a retiring job
   std::vector<Host<P>> hs;
   std::vector<Job*> slot_job;
   std::vector<int64_t> slot_done;  // steps completed by the job in the slot
@@ -1773,6 +1826,7 @@ struct Server : ServerBase {
     HD_TRY(hipMalloc((void**)&d_idle, sizeof(State) * (size_t)S));
     HD_TRY(hipMemset(d_idle, 0, sizeof(State) * (size_t)S));
     HD_TRY(hipMalloc((void**)&d_desc, sizeof(Disch<P>) * S));
+    if (int rc = host.reserve(readout_layout((size_t)nn_max, 1, (size_t)nb1_max).off[kRoParts])) return rc;
     hs.resize(S);
     slot_job.assign(S, nullptr);
     slot_done.assign(S, 0);
@@ -1913,8 +1967,6 @@ struct Server : ServerBase {
   int retire(int slot) {
     Host<P>& h = hs[slot];
     Job* job = slot_job[slot];
-    State st;
-    HD_TRY(hipMemcpy(&st, h.dd.st, sizeof(State), hipMemcpyDeviceToHost));
     const int nn = h.dd.nn;
     JobResult& r = job->res;
     r.n_e.resize(nn);
@@ -1938,14 +1990,17 @@ struct Server : ServerBase {
     m.cnt = r.cnt.data();
     m.eedf_counts = r.eedf_counts.data();
     m.eedf = r.eedf.data();
-    const int rc = B::fill_moments(h, st, &m);
+    const Readout ro = B::readout_of(h);
+    HD_TRY(B::read_out(d_desc + slot, ro, m, host.p, stream));
+    B::fill_moments(h, ro, host.p, &m);
+    const State st = *reinterpret_cast<const State*>(host.p);
     const Disch<P> ie = idle_entry(slot);
     HD_TRY(hipMemcpy(d_desc + slot, &ie, sizeof(Disch<P>), hipMemcpyHostToDevice));
     mem.release(h.base);
     h.base = nullptr;
     std::lock_guard<std::mutex> g(mu);
     job->t_done = now_s();
-    job->err = st.error ? st.error : rc;
+    job->err = st.error;
     if (job->cancel) {
       job->state = 4;
       cancelled += 1;

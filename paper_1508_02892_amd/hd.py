@@ -291,17 +291,21 @@ def required_bytes(p: dict) -> int:
 
 
 class _Moments:
+    """A moment set and its arrays, which share one block of 8-byte elements
+    (the structure's array pointers, n_e to eedf, follow one another)."""
+    _ARRS = ("n_e", "n_i", "phi", "E", "gamma_i", "n_e_avg", "n_i_avg", "n_species",
+             "gamma_species", "cnt", "eedf_counts", "eedf")
+    _TYPES = {"cnt": np.int64, "eedf_counts": np.uint64}
+
     def __init__(self, nn, nb, K, S=1):
-        self.arrs = {k: np.zeros(nn) for k in ("n_e", "n_i", "phi", "E", "gamma_i", "n_e_avg",
-                                                 "n_i_avg")}
-        self.arrs["n_species"] = np.zeros(S * nn)
-        self.arrs["gamma_species"] = np.zeros(S * nn)
-        self.arrs["cnt"] = np.zeros(nn, np.int64)
-        self.arrs["eedf_counts"] = np.zeros(nb + 1, np.uint64)
-        self.arrs["eedf"] = np.zeros(nb)
+        size = [nn] * 7 + [S * nn] * 2 + [nn, nb + 1, nb]
+        end = np.cumsum(size)
+        block = np.zeros(end[-1])
+        self.arrs = {k: block[e - n:e].view(self._TYPES.get(k, np.float64))
+                     for k, n, e in zip(self._ARRS, size, end)}
         self.m = MomentSet()
-        for k, a in self.arrs.items():
-            setattr(self.m, k, a.ctypes.data_as(dict(MomentSet._fields_)[k]))
+        ptrs = np.frombuffer(self.m, np.uint64, len(size), MomentSet.n_e.offset)
+        ptrs[:] = block.ctypes.data + 8 * (end - size)
         self.K = K
 
     def result(self):
