@@ -349,15 +349,15 @@ typedef struct hd_launch_config {
                                7: as 3, with each chunk's collisions handled
                                before its velocities are written, in whole
                                64-byte segments.  These use 512-thread
-                               workgroups (chunks of 2,048 particles);
+                               workgroups (eight waves);
                                8 + v: variant v with 1,024-thread workgroups
-                               (chunks of 4,096), one per compute unit with
+                               (sixteen waves), one per compute unit with
                                four waves per SIMD where large grids leave
                                LDS for only one narrow workgroup (the
                                autotuner also tries them when the particle
                                state exceeds the MALL); FP32 only, and not
                                for variant 1 (9 is rejected)               */
-  int32_t electron_groups;  /* particle workgroups of the electron launch,
+  int32_t electron_groups;  /* workgroups of the electron launch,
                                1 .. 4096 (0: as many as fit on the device at
                                once)                                       */
   int32_t sort_groups;      /* workgroups of the sort's launches, 1 .. 65536

@@ -356,91 +356,95 @@ __host__ __device__ inline int tri_partitions(int n) {
 }
 constexpr int kTriRed = 128;  // max rows of the reduced system (2 x 64 partitions)
 
+// The serial sweeps below run on one wave and are bound by its instruction
+// issue (about 4.5 cycles each) and by LDS round trips, so they go in batches
+// of kSweep rows whose loads are issued together, without a predicate, at
+// constant offsets from pointers that advance once per batch.
+constexpr int kSweep = 4;
+
 // Thomas method for rows [0, n) of a x_{j-1} + b x_j + c x_{j+1} = d, one
-// reciprocal of the pivot per row; cp, dp are work arrays.  Rows are read
-// and written in full batches of B (LDS latency off the dependent chain).
-// Every lane that calls it computes the same values (callers run it on a
-// whole wave so that the running values stay in vector registers).
-template <int B>
-__device__ inline void thomas_serial(int n, const double* a, const double* b, const double* c,
-                                     const double* d, double* cp, double* dp, double* x) {
+// reciprocal of the pivot per row; cp, dp are work arrays.  Every lane that
+// calls it computes the same values (callers run it on a whole wave so that
+// the running values stay in vector registers).
+__device__ __forceinline__ void thomas_serial(int n, const double* a, const double* b,
+                                              const double* c, const double* d, double* cp,
+                                              double* dp, double* x) {
   double rr = 1.0 / b[0];
   double cpp = c[0] * rr, dpp = d[0] * rr;
   cp[0] = cpp;
   dp[0] = dpp;
-  int j = 1;
-  for (; j + B <= n; j += B) {
-    double av[B], bv[B], cv[B], dv[B];
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      av[u] = a[j + u];
-      bv[u] = b[j + u];
-      cv[u] = c[j + u];
-      dv[u] = d[j + u];
-    }
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      const double den = bv[u] - av[u] * cpp;
-      const double num = dv[u] - av[u] * dpp;
-      rr = 1.0 / den;
-      cpp = cv[u] * rr;
-      dpp = num * rr;
-      cv[u] = cpp;
-      dv[u] = dpp;
-    }
-#pragma unroll
-    for (int u = 0; u < B; ++u) {
-      cp[j + u] = cv[u];
-      dp[j + u] = dv[u];
-    }
-  }
-  for (; j < n; ++j) {
-    const double aj = a[j];
-    const double den = b[j] - aj * cpp;
-    const double num = d[j] - aj * dpp;
+  const double *pa = a + 1, *pb = b + 1, *pc = c + 1, *pd = d + 1;
+  double *qc = cp + 1, *qd = dp + 1;
+  auto row = [&](double av, double bv, double cv, double dv, int u) {
+    const double den = bv - av * cpp;
+    const double num = dv - av * dpp;
     rr = 1.0 / den;
-    cpp = c[j] * rr;
+    cpp = cv * rr;
     dpp = num * rr;
-    cp[j] = cpp;
-    dp[j] = dpp;
+    qc[u] = cpp;
+    qd[u] = dpp;
+  };
+  int j = 1;
+  for (; j + kSweep <= n; j += kSweep) {
+    double av[kSweep], bv[kSweep], cv[kSweep], dv[kSweep];
+#pragma unroll
+    for (int u = 0; u < kSweep; ++u) {
+      av[u] = pa[u];
+      bv[u] = pb[u];
+      cv[u] = pc[u];
+      dv[u] = pd[u];
+    }
+#pragma unroll
+    for (int u = 0; u < kSweep; ++u) row(av[u], bv[u], cv[u], dv[u], u);
+    pa += kSweep;
+    pb += kSweep;
+    pc += kSweep;
+    pd += kSweep;
+    qc += kSweep;
+    qd += kSweep;
   }
+  for (; j < n; ++j) row(*pa++, *pb++, *pc++, *pd++, 0), ++qc, ++qd;
   double xv = dpp;
   x[n - 1] = xv;
-  j = n - 2;
-  for (; j - B >= -1; j -= B) {
-    double cv[B], dv[B];
+  const double *rc = cp + n - 2, *rd = dp + n - 2;
+  double* rx = x + n - 2;
+  j = n - 1;  // rows left
+  for (; j >= kSweep; j -= kSweep) {
+    double cv[kSweep], dv[kSweep];
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
-      cv[u] = cp[j - u];
-      dv[u] = dp[j - u];
+    for (int u = 0; u < kSweep; ++u) {
+      cv[u] = rc[-u];
+      dv[u] = rd[-u];
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u) {
+    for (int u = 0; u < kSweep; ++u) {
       xv = dv[u] - cv[u] * xv;
-      dv[u] = xv;
+      rx[-u] = xv;
     }
-#pragma unroll
-    for (int u = 0; u < B; ++u) x[j - u] = dv[u];
+    rc -= kSweep;
+    rd -= kSweep;
+    rx -= kSweep;
   }
-  for (; j >= 0; --j) {
-    xv = dp[j] - cp[j] * xv;
-    x[j] = xv;
+  for (; j > 0; --j) {
+    xv = *rd-- - *rc-- * xv;
+    *rx-- = xv;
   }
 }
 
 // Exact partitioned solve of a_i x_{i-1} + b_i x_i + c_i x_{i+1} = d_i,
-// i < n, called by every thread of the workgroup (it synchronises inside).
-// Partition p = rows [p n / P, (p+1) n / P): lane p of wave 0 eliminates its
-// interior rows forward and backward so that each is x_i = D_i - A_i x_s -
-// C_i x_e in terms of the partition's first and last unknowns; the first and
-// last rows of all partitions form a 2P-row tridiagonal system solved by
-// wave 0; then every thread recovers interior unknowns.  a, c, d (LDS) are
-// overwritten with A, C, D; b receives the solution x.  red: 7 * kTriRed
-// doubles of LDS.  B: rows per batch of the serial sweeps.
-template <int B = 4>
-__device__ inline void solve_tridiag_block(int n, double* a, double* b, double* c, double* d,
-                                           double* red) {
-  const int tid = threadIdx.x, nt = blockDim.x;
+// i < n, called by every thread of the workgroup of NT (it synchronises
+// inside).  Partition p = rows [p n / P, (p+1) n / P): lane p of wave 0
+// eliminates its interior rows forward and backward so that each is x_i =
+// D_i - A_i x_s - C_i x_e in terms of the partition's first and last
+// unknowns; the first and last rows of all partitions form a 2P-row
+// tridiagonal system solved by wave 0; then every thread recovers interior
+// unknowns.  a, c, d (LDS) are overwritten with A, C, D; b receives the
+// solution x.  red: 7 * kTriRed doubles of LDS.  Partitions hold n / P rows or
+// one more, at least 4, so a sweep's batches are as many on every lane.
+template <int NT>
+__device__ __forceinline__ void solve_tridiag_block(int n, double* a, double* b, double* c,
+                                                    double* d, double* red) {
+  const int tid = threadIdx.x;
   // 0, but not known to be: keeps wave-0 serial values in vector registers
   const int zo = (int)(threadIdx.x / blockDim.x);
   const int P = tri_partitions(n);
@@ -456,7 +460,7 @@ __device__ inline void solve_tridiag_block(int n, double* a, double* b, double* 
     if (tid < 64) {
       if (tid == 0)
         for (int i = 0; i < n; ++i) rd[i] = d[i];
-      thomas_serial<B>(n, a + zo, b + zo, c + zo, rd + zo, rcp + zo, rdp + zo, b + zo);
+      thomas_serial(n, a + zo, b + zo, c + zo, rd + zo, rcp + zo, rdp + zo, b + zo);
     }
     __syncthreads();
     return;
@@ -465,84 +469,73 @@ __device__ inline void solve_tridiag_block(int n, double* a, double* b, double* 
     const int p = tid;
     const int s = p * n / P;
     const int e = (p + 1) * n / P - 1;
+    const int batches = (n / P - 4) / kSweep;  // of the n / P - 4 rows every lane sweeps
     // forward over the interior rows s+1 .. e-1
-    int i = s + 1;
-    double rr = 1.0 / b[i];
-    double ap = a[i] * rr, cp = c[i] * rr, dp = d[i] * rr;
-    a[i] = ap;
-    c[i] = cp;
-    d[i] = dp;
-    for (i = s + 2; i + B <= e; i += B) {
-      double av[B], bv[B], cv[B], dv[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        av[u] = a[i + u];
-        bv[u] = b[i + u];
-        cv[u] = c[i + u];
-        dv[u] = d[i + u];
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const double ai = av[u];
-        rr = 1.0 / (bv[u] - ai * cp);
-        ap = -(ai * ap) * rr;
-        cp = cv[u] * rr;
-        dp = (dv[u] - ai * dp) * rr;
-        av[u] = ap;
-        cv[u] = cp;
-        dv[u] = dp;
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        a[i + u] = av[u];
-        c[i + u] = cv[u];
-        d[i + u] = dv[u];
-      }
-    }
-    for (; i <= e - 1; ++i) {
-      const double ai = a[i], bi = b[i], ci = c[i], di = d[i];
+    double *pa = a + s + 1, *pb = b + s + 1, *pc = c + s + 1, *pd = d + s + 1;
+    double rr = 1.0 / *pb;
+    double ap = *pa * rr, cp = *pc * rr, dp = *pd * rr;
+    *pa = ap;
+    *pc = cp;
+    *pd = dp;
+    auto fwd = [&](double ai, double bi, double ci, double di, int u) {
       rr = 1.0 / (bi - ai * cp);
       ap = -(ai * ap) * rr;
       cp = ci * rr;
       dp = (di - ai * dp) * rr;
-      a[i] = ap;
-      c[i] = cp;
-      d[i] = dp;
+      pa[u] = ap;
+      pc[u] = cp;
+      pd[u] = dp;
+    };
+    ++pa, ++pb, ++pc, ++pd;
+    for (int k = 0; k < batches; ++k) {
+      double av[kSweep], bv[kSweep], cv[kSweep], dv[kSweep];
+#pragma unroll
+      for (int u = 0; u < kSweep; ++u) {
+        av[u] = pa[u];
+        bv[u] = pb[u];
+        cv[u] = pc[u];
+        dv[u] = pd[u];
+      }
+#pragma unroll
+      for (int u = 0; u < kSweep; ++u) fwd(av[u], bv[u], cv[u], dv[u], u);
+      pa += kSweep;
+      pb += kSweep;
+      pc += kSweep;
+      pd += kSweep;
+    }
+    for (int i = s + 2 + batches * kSweep; i <= e - 1; ++i) {
+      fwd(*pa, *pb, *pc, *pd, 0);
+      ++pa, ++pb, ++pc, ++pd;
     }
     // backward: x_i = D_i - A_i x_s - C_i x_e
-    for (i = e - 2; i - B >= s; i -= B) {
-      double av[B], cv[B], dv[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        av[u] = a[i - u];
-        cv[u] = c[i - u];
-        dv[u] = d[i - u];
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const double ci = cv[u];
-        dp = dv[u] - ci * dp;
-        ap = av[u] - ci * ap;
-        cp = -(ci * cp);
-        dv[u] = dp;
-        av[u] = ap;
-        cv[u] = cp;
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        d[i - u] = dv[u];
-        a[i - u] = av[u];
-        c[i - u] = cv[u];
-      }
-    }
-    for (; i >= s + 1; --i) {
-      const double ci = c[i];
-      dp = d[i] - ci * dp;
-      ap = a[i] - ci * ap;
+    pa = a + e - 2;
+    pc = c + e - 2;
+    pd = d + e - 2;
+    auto bwd = [&](double ai, double ci, double di, int u) {
+      dp = di - ci * dp;
+      ap = ai - ci * ap;
       cp = -(ci * cp);
-      d[i] = dp;
-      a[i] = ap;
-      c[i] = cp;
+      pd[-u] = dp;
+      pa[-u] = ap;
+      pc[-u] = cp;
+    };
+    for (int k = 0; k < batches; ++k) {
+      double av[kSweep], cv[kSweep], dv[kSweep];
+#pragma unroll
+      for (int u = 0; u < kSweep; ++u) {
+        av[u] = pa[-u];
+        cv[u] = pc[-u];
+        dv[u] = pd[-u];
+      }
+#pragma unroll
+      for (int u = 0; u < kSweep; ++u) bwd(av[u], cv[u], dv[u], u);
+      pa -= kSweep;
+      pc -= kSweep;
+      pd -= kSweep;
+    }
+    for (int i = e - 2 - batches * kSweep; i >= s + 1; --i) {
+      bwd(*pa, *pc, *pd, 0);
+      --pa, --pc, --pd;
     }
     // first and last rows with x_{s+1}, x_{e-1} substituted
     ra[2 * p] = a[s];
@@ -556,9 +549,9 @@ __device__ inline void solve_tridiag_block(int n, double* a, double* b, double* 
   }
   __syncthreads();
   if (tid < 64)
-    thomas_serial<B>(2 * P, ra + zo, rb + zo, rc + zo, rd + zo, rcp + zo, rdp + zo, rx + zo);
+    thomas_serial(2 * P, ra + zo, rb + zo, rc + zo, rd + zo, rcp + zo, rdp + zo, rx + zo);
   __syncthreads();
-  for (int i = tid; i < n; i += nt) {
+  for (int i = tid; i < n; i += NT) {
     const int p = ((i + 1) * P - 1) / n;
     const int s = p * n / P;
     const int e = (p + 1) * n / P - 1;

@@ -14,6 +14,13 @@ constexpr int kElecThreads = 512;  // electron-kernel workgroup (8 waves)
 constexpr int kTile = kElecThreads * kPerThread;  // particles per chunk
 constexpr int kSub = 64 * kPerThread;  // particles of one wave in a chunk (a sub-chunk)
 constexpr int kElecWide = 8;  // electron launch variants kElecWide + v: kernel v, 1,024-thread workgroups
+constexpr int kElecThreadsWide = 2 * kElecThreads;
+constexpr int kElecKernels = 8;  // electron kernels per precision, kind and width
+constexpr int kElecVariants = kElecWide + kElecKernels;  // launch variants: narrow, then wide
+// Kinds of batch that the electron kernels are compiled for: any; three
+// channels without attachment and drift-diffusion ions (constant or fitted)
+// in every discharge; the same with the full fluid.
+enum { kElecAny = 0, kElecDd = 1, kElecFull = 2 };
 constexpr int kSeeMax = 4096;      // secondaries per wall per step
 constexpr int kMaxCells = 4096;    // cells per discharge
 constexpr int kMaxNodes = kMaxCells + 1;
@@ -23,6 +30,9 @@ constexpr int kSortTile = 4096;    // items per sort tile (one workgroup of the 
 constexpr int kFinThreads = 1024;  // field/finalize workgroup
 constexpr int kMaxSpecies = 4;     // ion species of the multi-species model
 constexpr int kMaxMu = 256;        // mobility-table points per species
+
+// Sub-chunks that hold n slots.
+__host__ __device__ inline uint32_t subs_of(uint32_t n) { return (n + (uint32_t)kSub - 1u) / (uint32_t)kSub; }
 
 // Mutable per-discharge scalars.  They live in device memory so that a
 // captured sequence of launches can advance without host involvement.
@@ -36,8 +46,8 @@ struct State {
   uint32_t n_kids;       // children created this step
   uint32_t n_see[2];     // secondaries emitted this step (left, right)
   uint32_t n_chunks;     // sub-chunks processed by the last electron launch
-  uint32_t seg_off;      // launch-wide index of this discharge's first chunk (last launch)
-  uint32_t seg_per;      // chunks per particle workgroup (last launch)
+  uint32_t pad1;
+  uint32_t seg_per;      // sub-chunks per workgroup (last electron launch)
   int32_t fin_ready;     // set by the end-of-step workgroup once its offsets are published
   uint32_t app_done;     // append workgroups finished with this discharge (this launch)
   int32_t buf;           // current particle buffer (0/1)
@@ -70,7 +80,7 @@ struct State {
   int32_t ckpt_due;    // checkpoint the coming interval's start (close to capacity)
   int32_t ckpt_valid;  // the checkpoint area holds the start of the current interval
   uint32_t prev_n_main;  // slots in use at the last interval's start
-  uint32_t pad1;
+  uint32_t pad2;
 };
 
 // Immutable constants and device pointers of one discharge.

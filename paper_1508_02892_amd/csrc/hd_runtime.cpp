@@ -31,10 +31,11 @@ size_t electron_lds_bytes(int D, int tab_max, int nn_max, int nb1_max, int fluid
                           int variant);
 template <class P>
 hipError_t launch_electron_impl(const Disch<P>* d_dev, int D, int grid, int tab_max, int nn_max,
-                                int nb1_max, int fluid_nn, int K_max, int variant, hipStream_t s);
+                                int nb1_max, int fluid_nn, int K_max, int variant, int kind,
+                                hipStream_t s);
 template <class P>
 int electron_occupancy(int tab_max, int nn_max, int nb1_max, int fluid_nn, int K_max, int D,
-                       int variant);
+                       int variant, int kind);
 int electron_variants();
 // The electron variant with nontemporal traffic of ids, cells and offsets
 // (drain, then load; velocities left to the caches), and the size of
@@ -47,10 +48,11 @@ constexpr uint64_t kMallBytes = 256ull << 20;
 // 1,024-thread workgroups) where v's workgroups fit only one per CU (large
 // grids) and the wide ones fit: sixteen waves per CU instead of eight.
 template <class P>
-int widen_variant(int v, int tab_max, int nn_max, int nb1_max, int fluid_nn, int K_max, int D) {
+int widen_variant(int v, int tab_max, int nn_max, int nb1_max, int fluid_nn, int K_max, int D,
+                  int kind) {
   if (v >= kElecWide) return v;
-  if (electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v) != 1) return v;
-  return electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v + kElecWide) >= 1
+  if (electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v, kind) != 1) return v;
+  return electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v + kElecWide, kind) >= 1
              ? v + kElecWide
              : v;
 }
@@ -148,6 +150,15 @@ int64_t rf_steps_of(const hd_params& p) {
 
 // Ion models that solve Eq (2.3) (tridiagonal scratch in LDS).
 bool full_fluid(int32_t m) { return m == HD_ION_FULL_CONST_NU || m == HD_ION_FULL_FIT_NU; }
+
+// The kind of batch that discharges like p make up.
+int elec_kind_of(const hd_params& p) {
+  if (p.n_channels != 3) return kElecAny;
+  for (int k = 0; k < 3; ++k)
+    if (p.channels[k].kind == HD_XS_ATTACHMENT) return kElecAny;
+  if (p.ion_model == HD_ION_DD_SPECIES) return kElecAny;
+  return full_fluid(p.ion_model) ? kElecFull : kElecDd;
+}
 
 bool validate(const hd_params* p, std::string& why) {
   if (!p) return (why = "null params"), false;
@@ -676,6 +687,7 @@ struct BatchBase {
   int tab_max = 0, nn_max = 0, nb1_max = 0, nc_max = 0, fluid_nn = 0, K_max = 1;
   int cus = 0;              // compute units of the device
   int elec_variant = 0;     // electron kernel variant (hd_launch_config)
+  int elec_kind = kElecAny; // the kernels' kind of batch
   uint64_t state_bytes = 0; // initial particle state of all discharges
   hd_launch_config launch{};  // the applied shapes, defaults resolved
   std::string tune_key;     // the batch's key in the autotuner's cache
@@ -881,6 +893,9 @@ struct Batch : BatchBase {
       if (full_fluid(h.p.ion_model)) fluid_nn = std::max(fluid_nn, h.p.n_cells + 1);
     }
     sort_every = hs[0].p.sort_every;
+    elec_kind = elec_kind_of(hs[0].p);
+    for (const auto& h : hs)
+      if (elec_kind_of(h.p) != elec_kind) elec_kind = kElecAny;
     // launch geometry
     hipDeviceProp_t prop;
     HD_TRY(hipGetDeviceProperties(&prop, device));
@@ -916,7 +931,7 @@ struct Batch : BatchBase {
       state_bytes = bytes;
       if (bytes > kMallBytes) lc0.electron_variant = kElecVariantStreaming;
       lc0.electron_variant = widen_variant<P>(lc0.electron_variant, tab_max, nn_max, nb1_max,
-                                              fluid_nn, K_max, D);
+                                              fluid_nn, K_max, D, elec_kind);
     }
     hd_launch_config lc{};
     if (!tune_lookup(tune_key, lc) || apply_launch(lc) != HD_OK) {
@@ -990,7 +1005,8 @@ struct Batch : BatchBase {
     if (c.electron_variant < 0 || c.electron_variant >= electron_variants())
       return fail(HD_EINVAL, "electron_variant out of range");
     const int occ =
-        electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, c.electron_variant);
+        electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, c.electron_variant,
+                              elec_kind);
     if (occ < 1) return fail(HD_EINVAL, "this electron kernel variant cannot be resident");
     if (c.electron_groups == 0) c.electron_groups = std::min(cus * occ, (int)kMaxSegs);
     if (c.sort_groups == 0) c.sort_groups = cus * 4;
@@ -1005,7 +1021,7 @@ struct Batch : BatchBase {
     if (c.append_groups < 1 || c.append_groups > cus)
       return fail(HD_EINVAL, "append_groups out of range");
     elec_variant = c.electron_variant;
-    grid_e = D + c.electron_groups;
+    grid_e = c.electron_groups;
     grid_s = c.sort_groups;
     tile_s = c.sort_tile;
     grid_a = c.append_groups;
@@ -1020,7 +1036,7 @@ struct Batch : BatchBase {
     if (ckpt) e = launch_checkpoint<P>(d_desc, D, 0, std::max(1, cus * 2), stream);
     if (e != hipSuccess) return e;
     e = launch_electron_impl<P>(d_desc, D, grid_e, tab_max, nn_max, nb1_max, fluid_nn, K_max,
-                                elec_variant, stream);
+                                elec_variant, elec_kind, stream);
     if (e != hipSuccess) return e;
     e = launch_finalize<P>(d_desc, D, 0, nn_max, grid_a, stream);
     if (e != hipSuccess) return e;
@@ -1481,7 +1497,7 @@ struct Batch : BatchBase {
       if (err == hipSuccess) err = hipEventRecord(e[0], stream);
       if (err == hipSuccess)
         err = launch_electron_impl<P>(d_desc, D, grid_e, tab_max, nn_max, nb1_max, fluid_nn,
-                                      K_max, elec_variant, stream);
+                                      K_max, elec_variant, elec_kind, stream);
       if (err == hipSuccess) err = hipEventRecord(e[1], stream);
       if (err == hipSuccess) err = hipEventRecord(e[2], stream);
       if (err == hipSuccess) err = launch_finalize<P>(d_desc, D, 0, nn_max, grid_a, stream);
@@ -1534,14 +1550,14 @@ struct Batch : BatchBase {
     };
     std::vector<Cand> ce, cs, ca;  // electron, sort, append candidates
     for (int v = 0; v < electron_variants(); ++v) {
-      const int occ = electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v);
+      const int occ = electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v, elec_kind);
       if (occ < 1) continue;
       // wide workgroups where the narrow ones fit once per CU or the
       // particle state streams from HBM (measured faster in both cases, and
       // slower where two narrow workgroups per CU work in the MALL), and
       // only as many as fit at once (fewer would leave CUs idle)
       if (v >= kElecWide && state_bytes <= kMallBytes &&
-          electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v - kElecWide) != 1)
+          electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, D, v - kElecWide, elec_kind) != 1)
         continue;
       const int full = std::min(cus * occ, (int)kMaxSegs);
       for (int g : {full, std::max(1, full * 3 / 4), std::max(1, full / 2)}) {
@@ -1593,13 +1609,13 @@ struct Batch : BatchBase {
       which[(size_t)s * 3] = ie;
       which[(size_t)s * 3 + 1] = ia;
       which[(size_t)s * 3 + 2] = is;
-      const int ge = D + ce[ie].c.electron_groups;
+      const int ge = ce[ie].c.electron_groups;
       if (host_step % sort_every == 0)
         err = launch_checkpoint<P>(d_desc, D, 0, std::max(1, cus * 2), stream);
       if (err == hipSuccess) err = hipEventRecord(e[0], stream);
       if (err == hipSuccess)
         err = launch_electron_impl<P>(d_desc, D, ge, tab_max, nn_max, nb1_max, fluid_nn, K_max,
-                                      ce[ie].c.electron_variant, stream);
+                                      ce[ie].c.electron_variant, elec_kind, stream);
       if (err == hipSuccess) err = hipEventRecord(e[1], stream);
       if (err == hipSuccess) err = hipEventRecord(e[2], stream);
       if (err == hipSuccess)
@@ -1733,11 +1749,10 @@ struct Server : ServerBase {
   std::vector<int64_t> slot_done;  // steps completed by the job in the slot
   int grid_e = 0, grid_a = 0, grid_s = 0, tab_max = 0, nn_max = 0, nb1_max = 0, nc_max = 0,
       fluid_nn = 0, K_max = 1;
-  // One interval over all slots, captured twice: with the default electron
-  // variant, and with nontemporal traffic of ids, cells and offsets for when
-  // the admitted jobs' particle state is larger than the MALL (results are
-  // the same).
-  hipGraphExec_t graph = nullptr, graph_nt = nullptr;
+  // One interval over all slots, captured for each [admitted jobs all of
+  // kind kElecDd][their particle state larger than the MALL: nontemporal
+  // traffic of ids, cells and offsets] (results are the same).
+  hipGraphExec_t graph[2][2] = {};
   std::mutex mu;
   std::condition_variable cv;
   std::thread worker;
@@ -1774,8 +1789,9 @@ struct Server : ServerBase {
     cv.notify_all();
     for (auto& t : preppers)
       if (t.joinable()) t.join();
-    if (graph) (void)hipGraphExecDestroy(graph);
-    if (graph_nt) (void)hipGraphExecDestroy(graph_nt);
+    for (auto& row : graph)
+      for (hipGraphExec_t g : row)
+        if (g) (void)hipGraphExecDestroy(g);
     for (auto& h : hs)
       if (h.base) mem.release(h.base);
     if (d_desc) (void)hipFree(d_desc);
@@ -1815,12 +1831,18 @@ struct Server : ServerBase {
     if (lds > (size_t)prop.sharedMemPerBlock) return fail(HD_EINVAL, "slot caps exceed LDS");
     HD_TRY(sort_set_lds<P>(nc_max, S));
     HD_TRY(finalize_set_lds<P>(nn_max));
-    const int occ = electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, S, 0);
-    if (occ < 1) return fail(HD_EDEVICE, "electron kernel cannot be resident");
-    const int v_plain = widen_variant<P>(0, tab_max, nn_max, nb1_max, fluid_nn, K_max, S);
-    const int v_stream =
-        widen_variant<P>(kElecVariantStreaming, tab_max, nn_max, nb1_max, fluid_nn, K_max, S);
-    grid_e = S + std::min(prop.multiProcessorCount * occ, (int)kMaxSegs);
+    int occ = 0;
+    int variant[2][2];  // [kind is kElecDd][streaming]
+    for (int q = 0; q < 2; ++q) {
+      const int kind = q ? kElecDd : kElecAny;
+      const int o = electron_occupancy<P>(tab_max, nn_max, nb1_max, fluid_nn, K_max, S, 0, kind);
+      if (o < 1) return fail(HD_EDEVICE, "electron kernel cannot be resident");
+      occ = q ? std::min(occ, o) : o;
+      for (int nt = 0; nt < 2; ++nt)
+        variant[q][nt] = widen_variant<P>(nt ? kElecVariantStreaming : 0, tab_max, nn_max, nb1_max,
+                                          fluid_nn, K_max, S, kind);
+    }
+    grid_e = std::min(prop.multiProcessorCount * occ, (int)kMaxSegs);
     grid_a = std::max(1, prop.multiProcessorCount / 4);
     grid_s = prop.multiProcessorCount * 4;
     HD_TRY(hipMalloc((void**)&d_idle, sizeof(State) * (size_t)S));
@@ -1833,14 +1855,15 @@ struct Server : ServerBase {
     std::vector<Disch<P>> v;
     for (int i = 0; i < S; ++i) v.push_back(idle_entry(i));
     HD_TRY(hipMemcpy(d_desc, v.data(), sizeof(Disch<P>) * S, hipMemcpyHostToDevice));
-    // capture one interval of sort_every steps over all slots, per variant
-    for (int nt = 0; nt < 2; ++nt) {
+    // capture one interval of sort_every steps over all slots, per kind and variant
+    for (int gi = 0; gi < 4; ++gi) {
+      const int q = gi >> 1, nt = gi & 1;
       hipGraph_t g = nullptr;
       HD_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
       hipError_t e = hipSuccess;
       for (int s = 0; s < cfg.sort_every && e == hipSuccess; ++s) {
         e = launch_electron_impl<P>(d_desc, S, grid_e, tab_max, nn_max, nb1_max, fluid_nn, K_max,
-                                    nt ? v_stream : v_plain, stream);
+                                    variant[q][nt], q ? kElecDd : kElecAny, stream);
         if (e == hipSuccess) e = launch_finalize<P>(d_desc, S, 0, nn_max, grid_a, stream);
         if (e == hipSuccess && s == cfg.sort_every - 1)
           e = launch_sort_impl<P>(d_desc, S, grid_s, kSortTile, nc_max, stream);
@@ -1848,7 +1871,7 @@ struct Server : ServerBase {
       const hipError_t e2 = hipStreamEndCapture(stream, &g);
       if (e != hipSuccess || e2 != hipSuccess)
         return fail(HD_EDEVICE, std::string("capture failed: ") + hipGetErrorString(e ? e : e2));
-      e = hipGraphInstantiate(nt ? &graph_nt : &graph, g, nullptr, nullptr, 0);
+      e = hipGraphInstantiate(&graph[q][nt], g, nullptr, nullptr, 0);
       (void)hipGraphDestroy(g);
       if (e != hipSuccess) return fail(HD_EDEVICE, hipGetErrorString(e));
     }
@@ -2048,9 +2071,13 @@ struct Server : ServerBase {
       // particle bytes of the admitted jobs (their initial loads): beyond the
       // MALL the interval runs the streaming electron variant
       uint64_t resident = 0;
+      bool dd = true;
       for (int s = 0; s < S; ++s)
-        if (slot_job[s]) resident += (uint64_t)slot_job[s]->p.n_macro * (8u + 4u * sizeof(P));
-      hipGraphExec_t run = resident > kMallBytes ? graph_nt : graph;
+        if (slot_job[s]) {
+          resident += (uint64_t)slot_job[s]->p.n_macro * (8u + 4u * sizeof(P));
+          dd = dd && elec_kind_of(slot_job[s]->p) == kElecDd;
+        }
+      hipGraphExec_t run = graph[dd ? 1 : 0][resident > kMallBytes ? 1 : 0];
       const double t0 = now_s();
       if (hipGraphLaunch(run, stream) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess)
         return set_error(HD_EDEVICE, "interval launch failed");

@@ -602,7 +602,7 @@ __device__ void append_blocks(const Disch<P>* __restrict__ ds, int D) {
       const int buf = st->buf;
       const uint32_t nch = st->n_chunks, base = st->append_base, idb = st->id_base;
       const uint32_t nk = st->n_kids, n0 = st->n_see[0], n1 = st->n_see[1];
-      const uint32_t soff = st->seg_off, sper = st->seg_per;
+      const uint32_t sper = st->seg_per;
       const Gp<uint32_t>* kids = gptr(d.chunk_kids);
       const Gp<uint32_t>* cbase = gptr(d.chunk_base);
       const Gp<uint32_t>* sbase = gptr(d.seg);
@@ -612,8 +612,7 @@ __device__ void append_blocks(const Disch<P>* __restrict__ ds, int D) {
         uint64_t live = __ballot(cnt != 0u);
         if (live == 0) continue;
         // offset = the workgroup's among all children + the sub-chunk's in it
-        const uint32_t cb =
-            cnt ? sbase[(soff + k / (uint32_t)(kTile / kSub)) / sper] + cbase[k] : 0u;
+        const uint32_t cb = cnt ? sbase[k / sper] + cbase[k] : 0u;
         while (live) {
           const int l = __ffsll((unsigned long long)live) - 1;
           live &= live - 1;
@@ -674,7 +673,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const Disch<P>* __rest
   const int cbuf0 = st->cbuf;
   const uint32_t n_main = st->n_main;
   const uint32_t next_id = st->next_id;
-  const uint32_t seg_off = st->seg_off, seg_per = st->seg_per;
+  const uint32_t seg_per = st->seg_per;
   const double wall_g = tid < 2 ? st->wall[tid] : 0.0;
   const double amp = st->volt_amp;
   const Gp<int64_t>* gc0 = gptr(d.cnt[0]);
@@ -738,10 +737,8 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const Disch<P>* __rest
     periods = st->rf_periods;
   }
   // the electron launch's per-workgroup child totals of this discharge
-  const uint32_t nchunk = field_only ? 0u : (n_main + (uint32_t)kTile - 1u) / (uint32_t)kTile;
-  const uint32_t nch = nchunk * (uint32_t)(kTile / kSub);  // sub-chunks
-  const uint32_t pb0 = nchunk ? seg_off / seg_per : 0u;
-  const uint32_t pb1 = nchunk ? (seg_off + nchunk - 1u) / seg_per + 1u : 0u;  // exclusive
+  const uint32_t nch = field_only ? 0u : subs_of(n_main);  // sub-chunks
+  const uint32_t pb1 = nch ? (nch - 1u) / seg_per + 1u : 0u;
   Gp<uint32_t>* gseg = gptr(d.seg);
   // Emission deposits into a grid of its own (EN, zeroed here), so that it
   // can run beside the deposit's other updates; this step's final deposit
@@ -868,7 +865,7 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(const Disch<P>* __rest
     uint32_t n_kids = 0;
     // windows of 64 kScanWin totals; lane l takes kScanWin consecutive ones
     // (a serial scan in registers), then one wave scan of the lane sums
-    for (uint32_t t0 = pb0; t0 < pb1; t0 += 64u * kScanWin) {
+    for (uint32_t t0 = 0; t0 < pb1; t0 += 64u * kScanWin) {
       const uint32_t k0 = t0 + lane * (uint32_t)kScanWin;
       uint32_t v[kScanWin];
 #pragma unroll
