@@ -25,7 +25,7 @@
 // general channel loop that a batch cannot need then takes no registers, and
 // no instruction cache, from its particle loop (all in one kernel: 297
 // scalars spilled to vector lanes and 119 VGPRs, by itself 129 and 94; the
-// launch of 12 discharges with 16 M electrons 123.3 to 119.2 us, of 512 small
+// launch of 12 discharges with 16 M electrons 123.3 to 119.2 us, of 64 small
 // ones 24.2 to 22.8, of 2^20 electrons on 512 cells 18.7 to 15.6 together
 // with range_length).
 #pragma once
