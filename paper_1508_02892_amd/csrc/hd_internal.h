@@ -11,15 +11,16 @@ constexpr int kMaxK = 16;          // collision channels
 constexpr int kThreads = 256;      // append workgroup
 constexpr int kPerThread = 4;      // particles per thread per chunk (vector loads)
 constexpr int kElecThreads = 512;  // electron-kernel workgroup (8 waves)
-constexpr int kTile = kElecThreads * kPerThread;  // particles per chunk
-constexpr int kSub = 64 * kPerThread;  // particles of one wave in a chunk (a sub-chunk)
+constexpr int kTile = kElecThreads * kPerThread;  // slots that eight waves work on at once
+constexpr int kSub = 64 * kPerThread;  // slots that a wave works on at once (a sub-chunk)
 constexpr int kElecWide = 8;  // electron launch variants kElecWide + v: kernel v, 1,024-thread workgroups
 constexpr int kElecThreadsWide = 2 * kElecThreads;
 constexpr int kElecKernels = 8;  // electron kernels per precision, kind and width
 constexpr int kElecVariants = kElecWide + kElecKernels;  // launch variants: narrow, then wide
 // Kinds of batch that the electron kernels are compiled for: any; three
 // channels without attachment and drift-diffusion ions (constant or fitted)
-// in every discharge; the same with the full fluid.
+// in every discharge; the same with the full fluid.  (Figures for one kernel
+// against three: k_electron.h.)
 enum { kElecAny = 0, kElecDd = 1, kElecFull = 2 };
 constexpr int kSeeMax = 4096;      // secondaries per wall per step
 constexpr int kMaxCells = 4096;    // cells per discharge

@@ -16,18 +16,18 @@
 // 2,048 cells and more, outlasted them; equal shares of 2,048-slot chunks left
 // a last round.  In us per launch, before and after: 2^23 electrons and the
 // full fluid 79.5 and 65.5 (the first steps; 62.4 and 62.9 once the discharge
-// has spread: there the particles' instructions bound it), 2^20 FP64 electrons
-// 49.6 and 36.4, 12 discharges with 16 M 127.8 and 119.2, 2^24 electrons 127.5
-// and 120.2, 12 channels and 4 species 52.6 and 51.1.
+// has spread: there the particles' instructions bound it), 2^21 FP64 electrons
+// and the fitted full fluid 49.6 and 36.4, 24 discharges with 2^24 electrons
+// 127.8 and 119.2, 17.8 M electrons on 4,096 cells 127.5 and 120.2, 12
+// channels and 4 species (2^22 electrons) 52.6 and 51.1.
 //
 // The kernels are compiled once per kind of batch (HD_ELEC_KIND, set by the
 // source that includes this file): the code of the ion fluids and of the
 // general channel loop that a batch cannot need then takes no registers, and
 // no instruction cache, from its particle loop (all in one kernel: 297
 // scalars spilled to vector lanes and 119 VGPRs, by itself 129 and 94; the
-// launch of 12 discharges with 16 M electrons 123.3 to 119.2 us, of 64 small
-// ones 24.2 to 22.8, of 2^20 electrons on 512 cells 18.7 to 15.6 together
-// with range_length).
+// launch of 24 discharges with 2^24 electrons 123.3 to 119.2 us, of 64 small
+// ones 24.2 to 22.8, of 17.8 M electrons on 4,096 cells 123.8 to 120.2).
 #pragma once
 
 #include <type_traits>
@@ -1271,7 +1271,9 @@ __device__ __forceinline__ void fluid_update(const Disch<P>& d, double* lds, uin
 }
 
 // An ion-fluid update in sub-chunks of particle work: what a workgroup could
-// do of those in its time.
+// do of those in its time, at 0.6 to 0.8 us per sub-chunk (the full fluid 29 us
+// at 2,047 rows and 38 beside the particles of a full launch, drift-diffusion 2
+// to 6 us).
 template <class P>
 __device__ __forceinline__ uint32_t fluid_subs(const Disch<P>& d) {
   const bool full = d.ion_model == HD_ION_FULL_CONST_NU || d.ion_model == HD_ION_FULL_FIT_NU;
@@ -1281,7 +1283,9 @@ __device__ __forceinline__ uint32_t fluid_subs(const Disch<P>& d) {
 // Length of the ranges of `all` units on G workgroups: one each while there
 // are workgroups enough, else at least one per wave (a workgroup sets up and
 // flushes in the time of one sub-chunk and works on as many as it has waves
-// at once).
+// at once).  Launches of 64 sub-chunks (16,384 electrons) take 13.0 us with
+// one each and 16.2 with eight; of 1,192 on 512 workgroups (305,043 electrons,
+// 1,471 cells) 19.3 with three each and 16.8 with eight.
 __device__ __forceinline__ uint32_t range_length(uint32_t all, uint32_t G, uint32_t waves) {
   return all <= G ? 1u : max(waves, (all + G - 1u) / G);
 }
