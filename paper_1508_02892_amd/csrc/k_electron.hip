@@ -54,11 +54,12 @@ int electron_occupancy(int tab_max, int nn_max, int nb1_max, int fluid_nn, int K
   const void* fk = elec_kernel_of(kind, sizeof(P) == 8, variant);
   if (!fk) return 0;  // no wide twin
   if (hipFuncSetAttribute(fk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-      hipSuccess)
+          hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk, elec_threads(variant), lds) !=
+          hipSuccess) {
+    (void)hipGetLastError();  // an answer, not an error for the next launch to report
     return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fk, elec_threads(variant), lds) !=
-      hipSuccess)
-    return 0;
+  }
   return nb;
 }
 
