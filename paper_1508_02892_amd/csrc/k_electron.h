@@ -49,6 +49,7 @@ constexpr int kTabLds = 1024;              // collision-table rows kept in LDS (
                                            // at 10 points per eV); higher rows via the cache
 constexpr uint32_t kKidsLds = 512;         // sub-chunk child counts of a segment kept in LDS
 static_assert(kKidsLds <= (uint32_t)kElecThreads, "the LDS counts are scanned in one round");
+static_assert(kSub <= 0xFFFF, "the LDS counts are 16 bits wide");
 
 // Workgroup barrier that orders LDS accesses only: the wave's global stores
 // may still be in flight when it passes, where __syncthreads waits for them.
@@ -92,15 +93,22 @@ struct ElecArgs {
   int K_max;      // max channels
   int tab_rows;   // collision-table rows held in LDS (tab_rows_lds)
   int waves;      // waves per workgroup (8, or 16 in the wide variants)
+  int over_pre;   // the fluid's arrays lie over the table of ranges too
 };
 
 struct Lds {
-  uint32_t pre, tab, ep, bins, q, eedf, ctr, kids, next, total;
+  uint32_t pre, tab, ep, bins, q, eedf, ctr, kids, fluid, total;
   uint32_t rows;  // collision-table rows held in LDS
 };
 
 // LDS counters: [0, kMaxK) collisions per channel, then these.
-enum { kCtrAbsL = kMaxK, kCtrAbsR, kCtrCreated, kCtrOverflow, kCtrPushed, kCtrN };
+// kCtrNext: sub-chunks of the segment that have been handed out.
+enum { kCtrAbsL = kMaxK, kCtrAbsR, kCtrCreated, kCtrOverflow, kCtrPushed, kCtrNext, kCtrN };
+
+// LDS of the full fluid on fluid_nn nodes.
+__host__ __device__ inline uint32_t fluid_lds(int fluid_nn) {
+  return fluid_nn ? (4u * (uint32_t)fluid_nn + 7u * (uint32_t)kTriRed) * 8u : 0u;
+}
 
 template <class P>
 __host__ __device__ inline Lds lds_layout(const ElecArgs& a) {
@@ -112,19 +120,19 @@ __host__ __device__ inline Lds lds_layout(const ElecArgs& a) {
   Lds L;
   L.rows = rows;
   L.pre = 0;
-  L.tab = al(L.pre + (uint32_t)(a.D + 2) * 4u);  // ranges, and their length
+  L.tab = al(L.pre + (uint32_t)(a.D + 1) * 4u);  // ends of the ranges, and their length
   L.ep = al(L.tab + tab_lds * (uint32_t)sizeof(P));
   L.bins = al(L.ep + (uint32_t)a.nn_max * (uint32_t)sizeof(P));
   L.q = al(L.bins + (uint32_t)a.nn_max * 8u);
   L.eedf = al(L.q + (uint32_t)a.waves * (uint32_t)kWQ * (uint32_t)sizeof(QEntry<P>));
   L.ctr = al(L.eedf + (uint32_t)a.nb1_max * 4u);
   L.kids = al(L.ctr + (uint32_t)kCtrN * 4u);
-  L.next = L.kids + kKidsLds * 4u;
-  L.total = al(L.next + 4u);
-  // the ion fluid's arrays lie over everything but pre: a, b, c, r of Eq (2.3)
-  // and the reduced system of the partitioned solve
-  const uint32_t fluid = a.fluid_nn ? (4u * (uint32_t)a.fluid_nn + 7u * (uint32_t)kTriRed) * 8u : 0u;
-  if (L.tab + fluid > L.total) L.total = al(L.tab + fluid);
+  L.total = al(L.kids + kKidsLds * 2u);
+  // the ion fluid's arrays (a, b, c, r of Eq (2.3) and the reduced system of
+  // the partitioned solve) lie over everything but pre, or over pre too
+  L.fluid = a.over_pre ? 0u : L.tab;
+  const uint32_t fluid = fluid_lds(a.fluid_nn);
+  if (L.fluid + fluid > L.total) L.total = al(L.fluid + fluid);
   return L;
 }
 
@@ -140,11 +148,16 @@ constexpr uint32_t kTabMinLds = 128;
 template <class P>
 ElecArgs elec_args(int D, int tab_max, int nn_max, int nb1_max, int fluid_nn, int K_max,
                    int waves) {
-  ElecArgs a{D, tab_max, nn_max, nb1_max, fluid_nn, K_max, kTabLds, waves};
-  const Lds L = lds_layout<P>(a);
+  ElecArgs a{D, tab_max, nn_max, nb1_max, fluid_nn, K_max, kTabLds, waves, 0};
   const uint32_t budget = waves > kElecThreads / 64 ? kOnePerCu : kTwoPerCu;
-  const uint32_t fluid =
-      L.tab + (fluid_nn ? (4u * (uint32_t)fluid_nn + 7u * (uint32_t)kTriRed) * 8u : 0u);
+  const uint32_t fluid = fluid_lds(fluid_nn);
+  // Beside the table of ranges the full fluid of a large grid may not fit the
+  // LDS where it does by itself; it then lies over the table, which must not
+  // be read again: the launch then has D workgroups more, one for every range.
+  const uint32_t beside = lds_layout<P>(a).tab + fluid;
+  for (uint32_t limit : {budget, kOnePerCu})
+    if (fluid <= limit && beside > limit) a.over_pre = 1;
+  const Lds L = lds_layout<P>(a);
   if (L.total > budget && fluid <= budget) {
     const uint32_t rest = L.total - (L.ep - L.tab);  // everything but the table
     const uint32_t row = (uint32_t)K_max * (uint32_t)sizeof(P);
@@ -180,7 +193,7 @@ struct Seg {
   uint32_t ion_mask;  // bit k: channel k is an ionization
   uint32_t att_mask;  // bit k: channel k is an attachment
   uint32_t seed_lo, seed_hi, step, n_main;
-  uint32_t* kl;       // LDS copy of the segment's first kKidsLds sub-chunk child counts
+  uint16_t* kl;       // LDS copy of the segment's first kKidsLds sub-chunk child counts
   uint32_t kbase;     // index of the segment's first sub-chunk
   bool sample;
 };
@@ -608,7 +621,7 @@ __device__ __forceinline__ void wave_chunk(const Disch<P>& d, const Seg<P>& g, u
   }
   if (lane == 0) {
     gptr(d.chunk_kids)[u] = nk;
-    if (u - g.kbase < kKidsLds) g.kl[u - g.kbase] = nk;
+    if (u - g.kbase < kKidsLds) g.kl[u - g.kbase] = (uint16_t)nk;
   }
   if constexpr (!SW) {
     // Queue the collisions for drain().  A wave queues about five per
@@ -812,15 +825,13 @@ __device__ __forceinline__ void segment(const Disch<P>& d, uint32_t u0, uint32_t
   g.step = uni((uint32_t)st->step);
   g.n_main = uni(st->n_main);
   g.sample = uni(((st->step + 1) % d.eedf_every) == 0 ? 1u : 0u) != 0u;
-  g.kl = reinterpret_cast<uint32_t*>(smem + L.kids);
+  g.kl = reinterpret_cast<uint16_t*>(smem + L.kids);
   g.kbase = u0;
-  uint32_t* next = reinterpret_cast<uint32_t*>(smem + L.next);  // sub-chunks handed out
   QEntry<P>* q = reinterpret_cast<QEntry<P>*>(smem + L.q) + (size_t)wv * kWQ;
   lds_copy2<W * 64>(tab, gptr(d.tab), g.tab_rows * d.K, ep, gptr(d.Ep), d.nn);
   for (int i = tid; i < d.nn; i += nt) g.bins[i] = 0;
   for (int i = tid; i <= d.nbins; i += nt) g.eedf[i] = 0;
-  if (tid < kCtrN) g.ctr[tid] = 0;
-  if (tid == 0) *next = 2u * (uint32_t)W;
+  if (tid < kCtrN) g.ctr[tid] = tid == kCtrNext ? 2u * (uint32_t)W : 0u;
   // the deposit grid's pointer goes to scalar registers now, so that no wait
   // for it (and for the particle stores in flight behind it) is left for the
   // flush at the end
@@ -838,7 +849,7 @@ __device__ __forceinline__ void segment(const Disch<P>& d, uint32_t u0, uint32_t
       if (u < u1) chunk_load<P, (M & 4) != 0, (M & 8) != 0>(g, u, nx);
     while (u < u1) {
       uint32_t t = 0, n_short = 0;
-      if ((tid & 63) == 0) t = atomicAdd(next, 1u);
+      if ((tid & 63) == 0) t = atomicAdd(&g.ctr[kCtrNext], 1u);
       wave_chunk<P, KC, M>(d, g, u, q, qn, n_short, wc, nx, un, un < u1);
       if constexpr ((M & 16) == 0) drain<P, KC == 0>(d, g, q, qn, n_short, un < u1 ? 64u : 1u);
       u = un;
@@ -1253,6 +1264,7 @@ __device__ __forceinline__ void fluid_species(const Disch<P>& d, double* lds, in
 // The ion fluid of discharge d, in lds_bytes of LDS.
 template <int NT, int Q, class P>
 __device__ __forceinline__ void fluid_update(const Disch<P>& d, double* lds, uint32_t lds_bytes) {
+  lds_barrier();  // the arrays may lie over the table of ranges that other waves still read
   // a long chain beside the issue-bound waves of the CU's other workgroup
   __builtin_amdgcn_s_setprio(3);
   if constexpr (Q == kElecDd) {
@@ -1295,10 +1307,10 @@ __device__ __forceinline__ uint32_t range_length(uint32_t all, uint32_t G, uint3
 // one with the last unit updates the fluid.  A workgroup thus sets up and
 // flushes for one discharge only.  per is the smallest of ceil(U/G),
 // ceil(U/(G - D/2)), ceil(U/(G - D)) (U units in all, G workgroups) for which
-// there is a workgroup for every range (the last one always); with fewer
-// workgroups than that, each takes every G-th range.  Called by one wave:
-// pre[i] gets the first range of discharge i, pre[D] their number, pre[D + 1]
-// per.
+// there is a workgroup for every range (the last one always, if G > D); with
+// fewer workgroups than that, each takes every G-th range.  Called by one wave:
+// pre[i] gets the end of discharge i's ranges, pre[D - 1] thus their number,
+// pre[D] per.
 template <class P>
 __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, uint32_t G,
                                        uint32_t waves, uint32_t* pre) {
@@ -1322,7 +1334,8 @@ __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, u
     }
     return n;
   };
-  auto length = [&](uint32_t g) { return range_length(all, g, waves); };
+  // (a discharge has room for the totals of kMaxSegs ranges)
+  auto length = [&](uint32_t g) { return range_length(all, min(g, (uint32_t)kMaxSegs), waves); };
   uint32_t per = length(G);
   const uint32_t Du = (uint32_t)D;
   if (D > 1 && number(per) > G) {
@@ -1338,13 +1351,10 @@ __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, u
       const uint32_t y = __shfl_up(x, o, 64);
       if (lane >= o) x += y;
     }
-    if (b + lane < D) pre[b + lane + 1] = carry + x;
+    if (b + lane < D) pre[b + lane] = carry + x;
     carry += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
   }
-  if (lane == 0) {
-    pre[0] = 0;
-    pre[D + 1] = per;
-  }
+  if (lane == 0) pre[D] = per;
 }
 
 template <class P, int M, int W, int Q>
@@ -1353,7 +1363,7 @@ __device__ __forceinline__ void electron_body(const Disch<P>* __restrict__ ds, c
   const int D = a.D;
   const int tid = threadIdx.x;
   const Lds L = lds_layout<P>(a);
-  // first range of each discharge, their number, their length
+  // end of each discharge's ranges, their length
   uint32_t* pre = reinterpret_cast<uint32_t*>(smem + L.pre);
   if (D > 1) {
     if (tid < 64) ranges<P>(ds, D, gridDim.x, (uint32_t)W, pre);
@@ -1379,24 +1389,24 @@ __device__ __forceinline__ void electron_body(const Disch<P>* __restrict__ ds, c
       last = v == 0;
       r = last ? n - 1u : v - 1u;
     } else {
-      if (v >= uni(vpre[D])) return;
+      if (v >= uni(vpre[D - 1])) return;
       for (int b = 0; b < D; b += 64) {  // the discharges that end at or before range v
         const int i = b + (tid & 63);
-        di += (int)__popcll(__ballot(i < D && pre[i + 1] <= v));
+        di += (int)__popcll(__ballot(i < D && pre[i] <= v));
       }
-      per = uni(pre[D + 1]);
-      r = v - uni(pre[di]);
-      last = v + 1u == uni(pre[di + 1]);
+      per = uni(pre[D]);
+      r = v - (di ? uni(vpre[di - 1]) : 0u);
+      last = v + 1u == uni(pre[di]);
     }
     const Disch<P>& d = ds[di];
     const uint32_t u0 = r * per, u1 = min(subs_of(uni(d.st->n_main)), u0 + per);
     if (last) {
-      fluid_update<W * 64, Q>(d, reinterpret_cast<double*>(smem + L.tab), L.total - L.tab);
+      fluid_update<W * 64, Q>(d, reinterpret_cast<double*>(smem + L.fluid), L.total - L.fluid);
     }
     if (u0 < u1) segment<P, M, W, Q>(d, u0, u1, smem, L, r, per);
     // a single discharge has no more ranges than workgroups (and reading its
     // state again would wait behind the counters all workgroups add to)
-    if (D == 1) return;
+    if (D == 1 || a.over_pre) return;
   }
 }
 
