@@ -42,7 +42,7 @@ hipError_t launch_electron_impl(const Disch<P>* d_dev, int D, int grid, int tab_
   const Disch<P>* ds = d_dev;
   ElecArgs args = a;
   void* av[2] = {&ds, &args};
-  if (a.over_pre) grid += D;  // a workgroup for every range
+  if (a.over_pre && D > 1) grid += D;  // a workgroup for every range
   return hipLaunchKernel(fk, dim3(grid), dim3(nt), av, lds, s);
 }
 

@@ -76,3 +76,18 @@ def test_fluid_over_the_table_of_ranges(precision, cells, groups):
         orc.step(19)
         compare(b.moments(i), b.particles(i), orc)
     b.close()
+
+
+def test_fluid_over_the_table_of_one_discharge():
+    # 4,097 units of work on the most workgroups there can be: no more ranges
+    # than a discharge has room for the totals of
+    nodes = 2304
+    fluid = nodes // 32 + 4
+    p = W.small(precision=W.FP32, ion_model=W.ION_FULL, n_cells=nodes - 1, gap_m=1e-3, t_e0_eV=20.0,
+                n_macro=256 * (4097 - fluid), load_lo=0.0, load_hi=1.0, capacity=256 * 4200)
+    dev, orc = hd.Discharge(p), oracle.Oracle(p, contract=True)
+    dev.set_launch({"electron_groups": 4096})
+    dev.step(5)
+    orc.step(5)
+    compare(dev.moments(), dev.particles(), orc)
+    dev.close()
