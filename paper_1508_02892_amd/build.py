@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libhd.so")
 BUILD = os.path.join(HERE, "_build")
 SOURCES = ["k_electron.hip", "k_electron_dd.hip", "k_electron_full.hip", "k_field.hip", "k_sort.hip", "k_swarm.hip", "k_readout.hip", "hd_runtime.cpp"]
-HEADERS = ["hd_internal.h", "hd_device.h", "k_electron.h"]
+HEADERS = ["hd_internal.h", "hd_device.h", "k_electron.h", "work_split.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off",

@@ -34,6 +34,7 @@
 
 #include "hd.h"
 #include "hd_device.h"
+#include "work_split.h"
 
 namespace hd {
 
@@ -1292,28 +1293,19 @@ __device__ __forceinline__ uint32_t fluid_subs(const Disch<P>& d) {
   return (uint32_t)(full ? d.nn / 32 + 4 : d.nn / 512 + 4);
 }
 
-// Length of the ranges of `all` units on G workgroups: one each while there
-// are workgroups enough, else at least one per wave (a workgroup sets up and
-// flushes in the time of one sub-chunk and works on as many as it has waves
-// at once).  Launches of 64 sub-chunks (16,384 electrons) take 13.0 us with
-// one each and 16.2 with eight; of 1,192 on 512 workgroups (305,043 electrons,
-// 1,471 cells) 19.3 with three each and 16.8 with eight.
-__device__ __forceinline__ uint32_t range_length(uint32_t all, uint32_t G, uint32_t waves) {
-  return all <= G ? 1u : max(waves, (all + G - 1u) / G);
-}
-
 // The work of discharge i is its sub-chunks and then its fluid update, counted
 // as fluid_subs more; ranges of `per` go to consecutive workgroups, and the
 // one with the last unit updates the fluid.  A workgroup thus sets up and
-// flushes for one discharge only.  per is the smallest of ceil(U/G),
-// ceil(U/(G - D/2)), ceil(U/(G - D)) (U units in all, G workgroups) for which
-// there is a workgroup for every range (the last one always, if G > D); with
-// fewer workgroups than that, each takes every G-th range.  Called by one wave:
-// pre[i] gets the end of discharge i's ranges, pre[D - 1] thus their number,
-// pre[D] per.
+// flushes for one discharge at a time.  per is ceil(U/G) (U units in all, G
+// workgroups) where that makes no more than G ranges, else what batch_length
+// finds; with more ranges than workgroups, each takes every G-th.  (With ranges
+// for G workgroups whatever the discharges, one of 2^20 electrons among 599 of
+// 2,048 was one range: 1,830 us per step instead of 122.)  Called by one
+// wave: pre[i] gets the end of discharge i's ranges, pre[D - 1] thus their
+// number, pre[D] per.
 template <class P>
 __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, uint32_t G,
-                                       uint32_t waves, uint32_t* pre) {
+                                       uint32_t waves, uint32_t most_rounds, uint32_t* pre) {
   const int lane = threadIdx.x & 63;
   auto units = [&](int i) {  // none when the discharge has no steps left
     const State* st = ds[i].st;
@@ -1321,15 +1313,21 @@ __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, u
     const uint32_t u = subs_of(st->n_main) + fluid_subs(ds[i]);
     return left > 0 ? u : 0u;
   };
+  // the units of 64 discharges stay in a register, of more in pre until the
+  // ends replace them
   uint32_t all = 0, u = 0;
   for (int b = 0; b < D; b += 64) {
     u = b + lane < D ? units(b + lane) : 0u;
+    if (D > 64 && b + lane < D) pre[b + lane] = u;
     all += wave_sum_u32(u);
   }
+  auto again = [&](int b) {
+    if (D > 64) u = b + lane < D ? pre[b + lane] : 0u;
+  };
   auto number = [&](uint32_t per) {
     uint32_t n = 0;
     for (int b = 0; b < D; b += 64) {
-      if (D > 64) u = b + lane < D ? units(b + lane) : 0u;
+      again(b);
       n += wave_sum_u32((u + per - 1u) / per);
     }
     return n;
@@ -1337,14 +1335,18 @@ __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, u
   // (a discharge has room for the totals of kMaxSegs ranges)
   auto length = [&](uint32_t g) { return range_length(all, min(g, (uint32_t)kMaxSegs), waves); };
   uint32_t per = length(G);
-  const uint32_t Du = (uint32_t)D;
-  if (D > 1 && number(per) > G) {
-    per = length(G > Du / 2u ? G - Du / 2u : 1u);
-    if (number(per) > G) per = length(G > Du ? G - Du : 1u);
+  if (number(per) > G) {
+    uint32_t longest = 0, active = 0;
+    for (int b = 0; b < D; b += 64) {
+      again(b);
+      longest = max(longest, (uint32_t)-wave_min_i32(-(int)u));
+      active += (uint32_t)__popcll(__ballot(u != 0u));
+    }
+    per = batch_length(all, longest, active, G, most_rounds, length, number);
   }
   uint32_t carry = 0;
   for (int b = 0; b < D; b += 64) {
-    if (D > 64) u = b + lane < D ? units(b + lane) : 0u;
+    again(b);
     uint32_t x = (u + per - 1u) / per;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -1366,7 +1368,7 @@ __device__ __forceinline__ void electron_body(const Disch<P>* __restrict__ ds, c
   // end of each discharge's ranges, their length
   uint32_t* pre = reinterpret_cast<uint32_t*>(smem + L.pre);
   if (D > 1) {
-    if (tid < 64) ranges<P>(ds, D, gridDim.x, (uint32_t)W, pre);
+    if (tid < 64) ranges<P>(ds, D, gridDim.x, (uint32_t)W, a.over_pre ? 1u : ~0u, pre);
     lds_barrier();
   }
   // The loop's state is read back from LDS each time round, so that it takes

@@ -61,3 +61,19 @@ def test_work_split(name, ps, cfg):
         orc.step(19)
         compare(b.moments(i), b.particles(i), orc)
     b.close()
+
+
+@pytest.mark.parametrize("small,precision,groups", [(130, 0, 64), (700, 1, 0)],
+                         ids=["several rounds of ranges", "more discharges than workgroups"])
+def test_one_large_discharge_among_many(small, precision, groups):
+    # ranges shorter than the large discharge and more of them than workgroups
+    ps = [_p(1 + i % 300, seed=200 + i, precision=precision) for i in range(small)]
+    ps.insert(small // 2, _p(60_000, precision=precision, seed=9))
+    b = hd.Batch(ps)
+    b.set_launch({"electron_groups": groups})
+    b.step(19)
+    for i in (0, small // 2, small):
+        orc = oracle.Oracle(ps[i], contract=True)
+        orc.step(19)
+        compare(b.moments(i), b.particles(i), orc)
+    b.close()
