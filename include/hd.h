@@ -357,9 +357,11 @@ typedef struct hd_launch_config {
                                autotuner also tries them when the particle
                                state exceeds the MALL); FP32 only, and not
                                for variant 1 (9 is rejected)               */
-  int32_t electron_groups;  /* workgroups of the electron launch,
-                               1 .. 4096 (0: as many as fit on the device at
-                               once)                                       */
+  int32_t electron_groups;  /* workgroups that the electron launch divides
+                               its work for, 1 .. 4096 (0: as many as fit on
+                               the device at once); a batch of more than an
+                               eighth as many discharges may take one more
+                               per discharge                               */
   int32_t sort_groups;      /* workgroups of the sort's launches, 1 .. 65536
                                (0: four per compute unit)                  */
   int32_t append_groups;    /* workgroups that append new particles in the

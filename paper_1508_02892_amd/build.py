@@ -32,7 +32,18 @@ FLAGS = [
 # loads depend on its arguments: preloading them into scalar registers at
 # wave launch saves a memory round trip on its critical path (about 1 us per
 # step measured on the 8.4M-electron workload; no gain measured elsewhere).
+#
+# The electron kernels are short of scalar registers.  Constants moved out of
+# their loops to the kernel's start are spilled there and read back where they
+# are used; left where they are used they cost a scalar move beside the vector
+# work (12 channels, FP32: 89 spills instead of 124, 2^22 electrons 62.7 us per
+# step instead of 63.4; FP64, three channels: 43 instead of 53, 3 M electrons
+# 59.2 us instead of 61.6).
+_ELECTRON = ["-mllvm", "-disable-machine-licm"]
 SOURCE_FLAGS = {
+    "k_electron.hip": _ELECTRON,
+    "k_electron_dd.hip": _ELECTRON,
+    "k_electron_full.hip": _ELECTRON,
     "k_field.hip": ["-mllvm", "-amdgpu-kernarg-preload-count=4"],
 }
 

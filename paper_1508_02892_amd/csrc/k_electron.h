@@ -94,11 +94,11 @@ struct ElecArgs {
   int K_max;      // max channels
   int tab_rows;   // collision-table rows held in LDS (tab_rows_lds)
   int waves;      // waves per workgroup (8, or 16 in the wide variants)
-  int over_pre;   // the fluid's arrays lie over the table of ranges too
+  int groups;     // workgroups that the work is divided for (launch_groups: of the launch)
 };
 
 struct Lds {
-  uint32_t pre, tab, ep, bins, q, eedf, ctr, kids, fluid, total;
+  uint32_t pre, tab, ep, bins, q, eedf, ctr, kids, total;
   uint32_t rows;  // collision-table rows held in LDS
 };
 
@@ -130,10 +130,9 @@ __host__ __device__ inline Lds lds_layout(const ElecArgs& a) {
   L.kids = al(L.ctr + (uint32_t)kCtrN * 4u);
   L.total = al(L.kids + kKidsLds * 2u);
   // the ion fluid's arrays (a, b, c, r of Eq (2.3) and the reduced system of
-  // the partitioned solve) lie over everything but pre, or over pre too
-  L.fluid = a.over_pre ? 0u : L.tab;
+  // the partitioned solve) lie over all of it
   const uint32_t fluid = fluid_lds(a.fluid_nn);
-  if (L.fluid + fluid > L.total) L.total = al(L.fluid + fluid);
+  if (fluid > L.total) L.total = al(fluid);
   return L;
 }
 
@@ -152,12 +151,6 @@ ElecArgs elec_args(int D, int tab_max, int nn_max, int nb1_max, int fluid_nn, in
   ElecArgs a{D, tab_max, nn_max, nb1_max, fluid_nn, K_max, kTabLds, waves, 0};
   const uint32_t budget = waves > kElecThreads / 64 ? kOnePerCu : kTwoPerCu;
   const uint32_t fluid = fluid_lds(fluid_nn);
-  // Beside the table of ranges the full fluid of a large grid may not fit the
-  // LDS where it does by itself; it then lies over the table, which must not
-  // be read again: the launch then has D workgroups more, one for every range.
-  const uint32_t beside = lds_layout<P>(a).tab + fluid;
-  for (uint32_t limit : {budget, kOnePerCu})
-    if (fluid <= limit && beside > limit) a.over_pre = 1;
   const Lds L = lds_layout<P>(a);
   if (L.total > budget && fluid <= budget) {
     const uint32_t rest = L.total - (L.ep - L.tab);  // everything but the table
@@ -927,7 +920,6 @@ __device__ __forceinline__ void segment(const Disch<P>& d, uint32_t u0, uint32_t
     atomicAdd(reinterpret_cast<unsigned long long*>(&st->overflow), (unsigned long long)ctr[tid]);
   if (tid == kCtrPushed && ctr[tid])
     atomicAdd(reinterpret_cast<unsigned long long*>(&st->pushed), (unsigned long long)ctr[tid]);
-  lds_barrier();  // the next segment of this workgroup reuses the LDS
 }
 
 // ---- ion fluid -----------------------------------------------------------
@@ -1265,7 +1257,7 @@ __device__ __forceinline__ void fluid_species(const Disch<P>& d, double* lds, in
 // The ion fluid of discharge d, in lds_bytes of LDS.
 template <int NT, int Q, class P>
 __device__ __forceinline__ void fluid_update(const Disch<P>& d, double* lds, uint32_t lds_bytes) {
-  lds_barrier();  // the arrays may lie over the table of ranges that other waves still read
+  lds_barrier();  // the arrays lie over the table of ranges that other waves still read
   // a long chain beside the issue-bound waves of the CU's other workgroup
   __builtin_amdgcn_s_setprio(3);
   if constexpr (Q == kElecDd) {
@@ -1290,64 +1282,82 @@ __device__ __forceinline__ void fluid_update(const Disch<P>& d, double* lds, uin
 template <class P>
 __device__ __forceinline__ uint32_t fluid_subs(const Disch<P>& d) {
   const bool full = d.ion_model == HD_ION_FULL_CONST_NU || d.ion_model == HD_ION_FULL_FIT_NU;
-  return (uint32_t)(full ? d.nn / 32 + 4 : d.nn / 512 + 4);
+  return (uint32_t)(full ? d.nn / 32 + 4 : d.nn / 512 + 4);  // at most 132
 }
 
-// The work of discharge i is its sub-chunks and then its fluid update, counted
-// as fluid_subs more; ranges of `per` go to consecutive workgroups, and the
-// one with the last unit updates the fluid.  A workgroup thus sets up and
-// flushes for one discharge at a time.  per is ceil(U/G) (U units in all, G
-// workgroups) where that makes no more than G ranges, else what batch_length
-// finds; with more ranges than workgroups, each takes every G-th.  (With ranges
-// for G workgroups whatever the discharges, one of 2^20 electrons among 599 of
-// 2,048 was one range: 1,830 us per step instead of 122.)  Called by one
-// wave: pre[i] gets the end of discharge i's ranges, pre[D - 1] thus their
-// number, pre[D] per.
+// Work of discharge i: its sub-chunks, and in the upper byte what its fluid
+// update counts as; none when it has no steps left.
+template <class P>
+__device__ __forceinline__ uint32_t work_of(const Disch<P>* __restrict__ ds, int i) {
+  const State* st = ds[i].st;
+  const int64_t left = st->steps_left;  // all loads issued together
+  const uint32_t w = subs_of(st->n_main) | fluid_subs(ds[i]) << 24;
+  return left > 0 ? w : 0u;
+}
+
+// The division of several discharges into ranges of `per` units, one for each
+// workgroup, which thus sets up and flushes for one discharge only.  The
+// discharges' last ranges, which update the fluids too, go to the first
+// workgroups; where the last units are the fluid's alone, those that share
+// their CUs have it to themselves for the most part (two discharges of
+// 262,144 electrons on 258 workgroups, 256 CUs: 29.8 us per step with each
+// last range after the others of its discharge, 28.1 so).  (With at most G ranges
+// whatever the discharges, one of 2^20 electrons among 599 of 2,048 was one
+// range: 1,830 us per step instead of 109.)  Called by one wave, with the
+// units of more than 64 discharges in pre: pre[i] gets, of the discharges up to
+// i, how many have units in its upper half and how many ranges beside the last
+// ones they have in its lower half (a launch has at most launch_groups, fewer
+// than 2^16), pre[D] per.
 template <class P>
 __device__ __forceinline__ void ranges(const Disch<P>* __restrict__ ds, int D, uint32_t G,
-                                       uint32_t waves, uint32_t most_rounds, uint32_t* pre) {
+                                       uint32_t waves, uint32_t* pre) {
   const int lane = threadIdx.x & 63;
-  auto units = [&](int i) {  // none when the discharge has no steps left
-    const State* st = ds[i].st;
-    const int64_t left = st->steps_left;  // all loads issued together
-    const uint32_t u = subs_of(st->n_main) + fluid_subs(ds[i]);
-    return left > 0 ? u : 0u;
+  uint32_t w = D <= 64 && lane < D ? work_of(ds, lane) : 0u;
+  uint32_t subs = 0, u = 0;  // of the lane's discharge: sub-chunks, units in all
+  auto load = [&](int b) {
+    if (D > 64) w = b + lane < D ? pre[b + lane] : 0u;
+    subs = w & 0xFFFFFFu;
+    u = subs + (w >> 24);
   };
-  // the units of 64 discharges stay in a register, of more in pre until the
-  // ends replace them
-  uint32_t all = 0, u = 0;
+  uint32_t all = 0, longest = 0, active = 0;
   for (int b = 0; b < D; b += 64) {
-    u = b + lane < D ? units(b + lane) : 0u;
-    if (D > 64 && b + lane < D) pre[b + lane] = u;
-    all += wave_sum_u32(u);
+    load(b);
+    all += u;
+    longest = max(longest, u);
+    active += u ? 1u : 0u;
   }
-  auto again = [&](int b) {
-    if (D > 64) u = b + lane < D ? pre[b + lane] : 0u;
-  };
+  all = wave_sum_u32(all);
+  active = wave_sum_u32(active);
+  longest = (uint32_t)-wave_min_i32(-(int)longest);
   auto number = [&](uint32_t per) {
     uint32_t n = 0;
+    const float inv = 1.0f / (float)per;
     for (int b = 0; b < D; b += 64) {
-      again(b);
-      n += wave_sum_u32((u + per - 1u) / per);
+      load(b);
+      n += ranges_in(u, per, inv);
     }
-    return n;
+    return wave_sum_u32(n);
   };
   // (a discharge has room for the totals of kMaxSegs ranges)
   auto length = [&](uint32_t g) { return range_length(all, min(g, (uint32_t)kMaxSegs), waves); };
-  uint32_t per = length(G);
-  if (number(per) > G) {
-    uint32_t longest = 0, active = 0;
-    for (int b = 0; b < D; b += 64) {
-      again(b);
-      longest = max(longest, (uint32_t)-wave_min_i32(-(int)u));
-      active += (uint32_t)__popcll(__ballot(u != 0u));
-    }
-    per = batch_length(all, longest, active, G, most_rounds, length, number);
+  // as for one discharge, a range for each fluid while there are workgroups enough
+  uint32_t per = max(1u, least_length(all, waves));
+  uint32_t own = 0;
+  float inv = 1.0f / (float)per;
+  for (int b = 0; b < D; b += 64) {
+    load(b);
+    own += ranges_in(subs, per, inv);
+  }
+  own = wave_sum_u32(own) + active <= G ? 1u : 0u;
+  if (!own) {
+    per = batch_length(all, longest, active, G, gridDim.x, length, number);
+    inv = 1.0f / (float)per;
   }
   uint32_t carry = 0;
   for (int b = 0; b < D; b += 64) {
-    again(b);
-    uint32_t x = (u + per - 1u) / per;
+    load(b);
+    // (1, ranges - 1)
+    uint32_t x = u ? 0xFFFFu + ranges_in(own ? subs : u, per, inv) + own : 0u;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t y = __shfl_up(x, o, 64);
@@ -1365,54 +1375,60 @@ __device__ __forceinline__ void electron_body(const Disch<P>* __restrict__ ds, c
   const int D = a.D;
   const int tid = threadIdx.x;
   const Lds L = lds_layout<P>(a);
-  // end of each discharge's ranges, their length
-  uint32_t* pre = reinterpret_cast<uint32_t*>(smem + L.pre);
-  if (D > 1) {
-    if (tid < 64) ranges<P>(ds, D, gridDim.x, (uint32_t)W, a.over_pre ? 1u : ~0u, pre);
+  // One range per workgroup, and no loop over ranges: the compiler hoisted
+  // what the fluids and the particle loop need out of it, to the kernel's
+  // start, where it spilled (three channels 140 scalars instead of 52, any
+  // batch 299 instead of 125; the launch of 800,000 electrons and twelve
+  // channels 24.9 us instead of 24.0, of two discharges of 262,144 18.7
+  // instead of 17.3).
+  const uint32_t v = blockIdx.x;
+  int di = 0;
+  uint32_t r, per;
+  bool last;
+  if (D == 1) {
+    // one discharge: no table of ranges, and its last range (the fluid's)
+    // goes to the workgroup that is started first
+    const State* st = ds[0].st;
+    const int64_t left = st->steps_left;
+    const uint32_t n_main = st->n_main;
+    const Ranges one = ranges_of_one(uni(subs_of(n_main)), fluid_subs(ds[0]), (uint32_t)a.groups,
+                                     (uint32_t)W);
+    if (uni(left > 0 ? 1u : 0u) == 0u || v >= one.n) return;
+    per = one.per;
+    last = v == 0;
+    r = last ? one.n - 1u : v - 1u;
+  } else {
+    // end of each discharge's ranges, their length
+    uint32_t* pre = reinterpret_cast<uint32_t*>(smem + L.pre);
+    if (D > 64) {  // by all waves: a round trip for 64 at a time would add up
+      for (int i = tid; i < D; i += W * 64) pre[i] = work_of(ds, i);
+      lds_barrier();
+    }
+    if (tid < 64) ranges<P>(ds, D, (uint32_t)a.groups, (uint32_t)W, pre);
     lds_barrier();
-  }
-  // The loop's state is read back from LDS each time round, so that it takes
-  // no scalar registers (all in use) from the ranges' code.
-  const volatile uint32_t* vpre = pre;
-  for (uint32_t v = blockIdx.x;; v += gridDim.x) {
-    int di = 0;
-    uint32_t r, per;
-    bool last;
-    if (D == 1) {
-      // one discharge: no table of ranges, and its last range (the fluid's)
-      // goes to the workgroup that is started first
-      const State* st = ds[0].st;
-      const int64_t left = st->steps_left;
-      const uint32_t n_main = st->n_main;
-      const uint32_t all = uni(subs_of(n_main)) + fluid_subs(ds[0]);
-      per = range_length(all, gridDim.x, (uint32_t)W);
-      const uint32_t n = (all + per - 1u) / per;
-      if (uni(left > 0 ? 1u : 0u) == 0u || v >= n) return;
-      last = v == 0;
-      r = last ? n - 1u : v - 1u;
-    } else {
-      if (v >= uni(vpre[D - 1])) return;
-      for (int b = 0; b < D; b += 64) {  // the discharges that end at or before range v
-        const int i = b + (tid & 63);
-        di += (int)__popcll(__ballot(i < D && pre[i] <= v));
-      }
-      per = uni(pre[D]);
-      r = v - (di ? uni(vpre[di - 1]) : 0u);
-      last = v + 1u == uni(pre[di]);
+    const uint32_t n = uni(pre[D - 1]), active = n >> 16;
+    last = v < active;
+    const uint32_t w = last ? v : v - active;
+    if (!last && w >= (n & 0xFFFFu)) return;
+    for (int b = 0; b < D; b += 64) {  // the discharges before the one of range w
+      const int i = b + (tid & 63);
+      const uint32_t e = i < D ? pre[i] : ~0u;
+      di += (int)__popcll(__ballot((last ? e >> 16 : e & 0xFFFFu) <= w));
     }
-    const Disch<P>& d = ds[di];
-    const uint32_t u0 = r * per, u1 = min(subs_of(uni(d.st->n_main)), u0 + per);
-    if (last) {
-      fluid_update<W * 64, Q>(d, reinterpret_cast<double*>(smem + L.fluid), L.total - L.fluid);
-    }
-    if (u0 < u1) segment<P, M, W, Q>(d, u0, u1, smem, L, r, per);
-    // a single discharge has no more ranges than workgroups (and reading its
-    // state again would wait behind the counters all workgroups add to)
-    if (D == 1 || a.over_pre) return;
+    per = uni(pre[D]);
+    const uint32_t before = di ? uni(pre[di - 1]) & 0xFFFFu : 0u;
+    r = last ? (uni(pre[di]) & 0xFFFFu) - before : w - before;
   }
+  const Disch<P>& d = ds[di];
+  const uint32_t u0 = r * per, u1 = min(subs_of(uni(d.st->n_main)), u0 + per);
+  if (last) fluid_update<W * 64, Q>(d, reinterpret_cast<double*>(smem), L.total);
+  if (u0 < u1) segment<P, M, W, Q>(d, u0, u1, smem, L, r, per);
 }
 
-// FP32: at most 128 VGPRs so that four waves share each SIMD.  Each kernel
+// FP32: at most 128 VGPRs so that four waves share each SIMD, and no more
+// waves, for which the compiler would save registers at the price of waits
+// (on 4,096 cells, where one wide workgroup has a CU, 161 us per step of 17.8 M
+// electrons instead of 159.7).  Each kernel
 // but the register-prefetch one has a wide twin (suffix _w): the same body
 // with 1,024-thread workgroups, one per CU, for grids whose LDS leaves room
 // for only one narrow workgroup per CU.
@@ -1422,11 +1438,11 @@ __device__ __forceinline__ void f32_body(const Disch<float>* __restrict__ ds, co
   electron_body<float, M, W, HD_ELEC_KIND>(ds, a, smem);
 }
 #define HD_F32_KERNEL(NAME, M)                                                                \
-  __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(4))) void     \
+  __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void     \
   NAME(const Disch<float>* __restrict__ ds, ElecArgs a) {                                    \
     f32_body<M, 8>(ds, a);                                                                   \
   }                                                                                          \
-  __global__ __launch_bounds__(kElecThreadsWide) __attribute__((amdgpu_waves_per_eu(4))) void \
+  __global__ __launch_bounds__(kElecThreadsWide) __attribute__((amdgpu_waves_per_eu(4, 4))) void \
   NAME##_w(const Disch<float>* __restrict__ ds, ElecArgs a) {                                \
     f32_body<M, 16>(ds, a);                                                                  \
   }
@@ -1452,53 +1468,23 @@ k_electron_f32_pf(const Disch<float>* __restrict__ ds, ElecArgs a) {
   f32_body<1, 8>(ds, a);
 }
 
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64(const Disch<double>* __restrict__ ds,
-                                                               ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 0, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_pf(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 1, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_nd(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 2, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_nt(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 12, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_nd_nt(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 14, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_np(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 4, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_nd_np(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 6, 8, HD_ELEC_KIND>(ds, a, smem);
-}
-
-__global__ __launch_bounds__(kElecThreads) void k_electron_f64_nt_sw(
-    const Disch<double>* __restrict__ ds, ElecArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  electron_body<double, 28, 8, HD_ELEC_KIND>(ds, a, smem);
-}
+// FP64: at most four waves per SIMD, so that the compiler does not save
+// registers for more at the price of waits.
+#define HD_F64_KERNEL(NAME, M)                                                                 \
+  __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(2, 4))) void   \
+  NAME(const Disch<double>* __restrict__ ds, ElecArgs a) {                                     \
+    extern __shared__ __align__(16) unsigned char smem[];                                      \
+    electron_body<double, M, 8, HD_ELEC_KIND>(ds, a, smem);                                    \
+  }
+HD_F64_KERNEL(k_electron_f64, 0)
+HD_F64_KERNEL(k_electron_f64_pf, 1)
+HD_F64_KERNEL(k_electron_f64_nd, 2)
+HD_F64_KERNEL(k_electron_f64_nt, 12)
+HD_F64_KERNEL(k_electron_f64_nd_nt, 14)
+HD_F64_KERNEL(k_electron_f64_np, 4)
+HD_F64_KERNEL(k_electron_f64_nd_np, 6)
+HD_F64_KERNEL(k_electron_f64_nt_sw, 28)
+#undef HD_F64_KERNEL
 
 // Kernels of one precision, by how the particle data arrive and leave:
 // 0 drain then load, 1 next chunk prefetched, 2 no drain; 3 and 4 as 0 and 2

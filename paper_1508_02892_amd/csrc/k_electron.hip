@@ -3,6 +3,8 @@
 #define HD_ELEC_KIND kElecAny
 #include "k_electron.h"
 
+#include <algorithm>
+
 namespace hd {
 
 HD_ELEC_EXPORT(elec_kernel_any)
@@ -42,7 +44,8 @@ hipError_t launch_electron_impl(const Disch<P>* d_dev, int D, int grid, int tab_
   const Disch<P>* ds = d_dev;
   ElecArgs args = a;
   void* av[2] = {&ds, &args};
-  if (a.over_pre && D > 1) grid += D;  // a workgroup for every range
+  args.groups = grid;
+  grid = (int)launch_groups((uint32_t)D, (uint32_t)grid);
   return hipLaunchKernel(fk, dim3(grid), dim3(nt), av, lds, s);
 }
 
@@ -61,7 +64,10 @@ int electron_occupancy(int tab_max, int nn_max, int nb1_max, int fluid_nn, int K
     (void)hipGetLastError();  // an answer, not an error for the next launch to report
     return 0;
   }
-  return nb;
+  // Sixteen waves per CU: on small grids, where the LDS has room for a third
+  // narrow workgroup, work divided for three per CU is slower (64 discharges
+  // of 16,384 electrons 39.8 us per step instead of 35.0).
+  return std::min(nb, 16 * 64 / elec_threads(variant));
 }
 
 int electron_variants() { return kElecVariants; }
