@@ -303,6 +303,86 @@ __global__ __launch_bounds__(kSwarmThreads, kSwarmBlocks<P>) void k_swarm_step(
     atomicAdd(reinterpret_cast<unsigned long long*>(&w.over[f]), (unsigned long long)cnt[1]);
 }
 
+// The same for a few steps of swarms of few ions, one ion per lane and the
+// lanes in step: bound by the launch and the chain of one step, which the
+// stages of k_swarm_step lengthen, while there is nothing for its lanes to be
+// apart for (launch_swarm_step).
+template <class P, bool ACC>
+__global__ __launch_bounds__(kSwarmThreads) void k_swarm_few(SwarmDev<P> w, uint32_t step0,
+                                                             uint32_t n_steps,
+                                                             uint32_t blocks_per_field) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  P* tab = reinterpret_cast<P*>(smem);
+  __shared__ uint32_t cnt[2];
+  const int tid = threadIdx.x;
+  for (int k = tid; k < w.ne; k += kSwarmThreads) tab[k] = w.tab[k];
+  if (tid < 2) cnt[tid] = 0u;
+  __syncthreads();
+  const uint32_t f = blockIdx.x / blocks_per_field;
+  const uint32_t i = (blockIdx.x - f * blocks_per_field) * kSwarmThreads + (uint32_t)tid;
+  uint32_t n_coll = 0, n_over = 0;
+  if ((int64_t)i < w.n_ions) {
+    const int64_t k = (int64_t)f * w.n_ions + i;
+    P vx = w.vx[k], vy = w.vy[k], vz = w.vz[k];
+    double az = ACC ? w.avz[k] : 0.0, a2 = ACC ? w.av2[k] : 0.0;
+    const P acc = w.a[f];
+    const P Pmax = w.Pmax, KEr = w.KEr, inv_dE = w.inv_dE, m1 = w.m1, m2 = w.m2;
+    const P top = (P)(w.ne - 1);
+    const uint32_t tag = kTagSwarm + 16u * f;
+    for (uint32_t s = 0; s < n_steps; ++s) {
+      StreamT<true> st(w.seed, tag, i, step0 + s);  // one ion per lane
+      vz = vz + acc;
+      const P u0 = Uni<P>::get(st);
+      if (u0 < Pmax) {
+        P tx, ty, tz;
+        maxwellian<P>(st, w.vth_n, tx, ty, tz);
+        const P gx = vx - tx, gy = vy - ty, gz = vz - tz;
+        const P g2 = (gx * gx + gy * gy) + gz * gz;
+        const P sc = (KEr * g2) * inv_dE;
+        int j;
+        P t;
+        if (!(sc < top)) {  // beyond the table (or not a number)
+          j = w.ne - 2;
+          t = (P)1;
+          n_over += 1u;
+        } else {
+          j = (int)sc;
+          t = sc - (P)j;
+        }
+        const P pc = tab[j] + t * (tab[j + 1] - tab[j]);
+        if (u0 < pc) {
+          P nx, ny, nz;
+          sphere<P>(st, nx, ny, nz);
+          const P r = m2 * sqrt(g2);
+          vx = (m1 * vx + m2 * tx) + r * nx;
+          vy = (m1 * vy + m2 * ty) + r * ny;
+          vz = (m1 * vz + m2 * tz) + r * nz;
+          n_coll += 1u;
+        }
+      }
+      if constexpr (ACC) {
+        const double x = (double)vx, y = (double)vy, z = (double)vz;
+        az = az + z;
+        a2 = a2 + ((x * x + y * y) + z * z);
+      }
+    }
+    w.vx[k] = vx;
+    w.vy[k] = vy;
+    w.vz[k] = vz;
+    if constexpr (ACC) {
+      w.avz[k] = az;
+      w.av2[k] = a2;
+    }
+  }
+  if (n_coll) atomicAdd(&cnt[0], n_coll);
+  if (n_over) atomicAdd(&cnt[1], n_over);
+  __syncthreads();
+  if (tid == 0 && cnt[0])
+    atomicAdd(reinterpret_cast<unsigned long long*>(&w.coll[f]), (unsigned long long)cnt[0]);
+  if (tid == 1 && cnt[1])
+    atomicAdd(reinterpret_cast<unsigned long long*>(&w.over[f]), (unsigned long long)cnt[1]);
+}
+
 // Clears the per-swarm counters and sums (a fill kernel rather than a
 // memset, so that the launch may be captured into a graph).
 template <class P>
@@ -380,11 +460,26 @@ template <class P>
 hipError_t launch_swarm_step(const SwarmDev<P>& w, uint32_t step0, int n_steps, int accumulate,
                              hipStream_t s) {
   constexpr int64_t waves = kSwarmThreads / 64, slots = kSwarmCus * kSwarmBlocks<P>;
+  const size_t lds = (size_t)w.ne * sizeof(P);
+  // A few steps with the lanes in step, unless a field's workgroups are so
+  // many that they wait for each other at its counters.  Where the lines lie,
+  // in us in step and apart: 7 x 2,048 ions 4 steps 25.9, 30.4, 8 steps 35.8,
+  // 38.0, 12 steps 46.4, 42.4; 300 x 2,048 (1.2 ions per lane of the device) 4
+  // steps 63.2, 64.3, 6 steps 84.8, 79.1; 1,100 x 1,024 (2.1) 2 steps 58.8, 62.8,
+  // 4 steps 94.8, 91.6; 16 x 65,536 (256 workgroups each) one step 63.0, 47.0.
+  constexpr int64_t lanes = slots * kSwarmThreads, kFewBlocks = 64;
+  const int64_t blocks = (w.n_ions + kSwarmThreads - 1) / kSwarmThreads;
+  const int64_t ions = (int64_t)w.n_fields * w.n_ions;
+  if (blocks <= kFewBlocks && n_steps <= 8 && (ions <= lanes || n_steps * ions <= 5 * lanes)) {
+    const auto k = accumulate ? k_swarm_few<P, true> : k_swarm_few<P, false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(blocks * w.n_fields)), dim3(kSwarmThreads), lds, s, w,
+                       step0, (uint32_t)n_steps, (uint32_t)blocks);
+    return hipGetLastError();
+  }
   const int64_t fit = slots / w.n_fields > 1 ? slots / w.n_fields : 1;  // workgroups per field
   const int64_t per = (w.n_ions + fit * kSwarmThreads - 1) / (fit * kSwarmThreads) * 64;
   const int64_t bpf = (w.n_ions + per * waves - 1) / (per * waves);
   const unsigned grid = (unsigned)(bpf * w.n_fields);
-  const size_t lds = (size_t)w.ne * sizeof(P);
   const auto k = accumulate ? k_swarm_step<P, true> : k_swarm_step<P, false>;
   hipLaunchKernelGGL(k, dim3(grid), dim3(kSwarmThreads), lds, s, w, step0, (uint32_t)n_steps,
                      (uint32_t)per, (uint32_t)bpf);

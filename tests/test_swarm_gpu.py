@@ -68,6 +68,21 @@ def test_ions_per_wave(precision, fields, n_ions, steps):
     _compare(dev, orc, fields)
 
 
+@pytest.mark.parametrize("precision,fields,n_ions,steps", [
+    (0, 1, 1, 1), (1, 3, 257, 8), (1, 3, 257, 9),        # few steps, and one more
+    (0, 1, 16384, 3), (0, 1, 16385, 3),                  # most workgroups of a field, and one more
+    (0, 640, 1024, 4), (0, 640, 1024, 5),                # more ions than lanes: 5 and 6.25 of them in all
+    (1, 7, 300, 1026),                                   # two steps after a whole launch
+])
+def test_few_steps(precision, fields, n_ions, steps):
+    p = W.swarm_params(np.linspace(0.0, 8e6, fields), n_ions=n_ions, precision=precision)
+    dev, orc = hd.Swarm(p), oracle.Swarm(p, contract=True)
+    for acc in (False, True):
+        dev.run(steps, accumulate=acc)
+        orc.run(steps, accumulate=acc)
+    _compare(dev, orc, fields)
+
+
 def test_table_overflow_matches():
     # a table ending at 0.16 eV: many candidates fall beyond it
     p = W.swarm_params([3e6], n_ions=1000, precision=0,
