@@ -388,7 +388,8 @@ int hd_batch_set_launch(hd_batch* b, const hd_launch_config* cfg);
  * The choice is applied, written to *out (may be NULL) and kept in a
  * process-wide cache keyed by the device and the batch's shape (precision,
  * discharges, particle count to a power of two, largest grid, channels,
- * ion models), which later handles with the same key start from.  If the
+ * ion models, the kernels' kind of batch, the library's division of work),
+ * which later handles with the same key start from.  If the
  * environment names a file in HD_TUNE_CACHE, the cache is also read from
  * and appended to that file. */
 int hd_batch_autotune(hd_batch* b, int64_t max_steps, hd_launch_config* out);

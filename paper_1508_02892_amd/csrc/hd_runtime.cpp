@@ -553,6 +553,10 @@ double volt_at(const hd_params& p, int64_t n) {
 // processes: one line "key variant electron_groups sort_groups append_groups
 // sort_tile" per choice, the last line of a key winning; a line without the
 // tile keeps the default tile).
+// Part of every key: choices made for another division of the launches' work
+// or other kernels say nothing about these, and a file may hold them for long.
+// 1: one range of sub-chunks per workgroup.
+constexpr int kTuneScheme = 1;
 std::mutex g_tune_mu;
 std::map<std::string, hd_launch_config> g_tune;
 bool g_tune_loaded = false;
@@ -918,7 +922,8 @@ struct Batch : BatchBase {
       for (const auto& h : hs) models |= 1 << h.p.ion_model;
       std::ostringstream k;
       k << prop.gcnArchName << ":" << cus << "/p" << precision << "/D" << D << "/n2^" << lg
-        << "/nc" << nc_max << "/K" << K_max << "/m" << models;
+        << "/nc" << nc_max << "/K" << K_max << "/m" << models << "/q" << elec_kind << "/s"
+        << kTuneScheme;
       tune_key = k.str();
     }
     // Untuned default: nontemporal traffic of ids, cells and offsets once the
