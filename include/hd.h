@@ -172,8 +172,11 @@ typedef struct hd_params {
  * least the sum of hd_required_bytes of its discharges; runs past 32,768
  * steps also take 8 bytes per step of the drive table from it, in doubling
  * increments (HD_ENOMEM from hd_step when it is exhausted).  The caller
- * keeps the arena alive and unused until the handle is freed.  NULL: the
- * library allocates.  The server and the ion swarm take no arena
+ * keeps the arena alive and unused until the handle is freed.  A handle also
+ * takes pinned host memory for its read-outs (8 to 14 words of 8 bytes per node
+ * and one per EEDF bin); that of a handle in an arena is kept when it is freed,
+ * up to 4 MB in all, for the next one, since freeing it would wait for all
+ * work on the device.  NULL: the library allocates.  The server and the ion swarm take no arena
  * (HD_EINVAL). */
 typedef struct hd_device_ctx {
   void* stream;

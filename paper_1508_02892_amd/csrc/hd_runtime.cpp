@@ -640,18 +640,67 @@ struct DevMem {
   }
 };
 
-// Pinned host memory of a handle that read-outs are written to.
+// Pinned host memory of a handle that read-outs are written to.  Freeing such
+// memory waits for everything on the device, which the release of a handle in
+// the caller's arena must not: its buffer is kept for later handles, up to
+// kMostKept of them and kKeptWords in all.  The release of any other handle waits anyway (hipFree), and
+// frees the kept buffers too.
 struct HostBuf {
   uint64_t* p = nullptr;
-  int reserve(size_t words) {
-    if (hipHostMalloc((void**)&p, words * 8, hipHostMallocDefault) != hipSuccess) {
+  size_t words = 0;
+  int device = 0;
+  bool in_arena = false;
+
+  struct Kept {
+    uint64_t* p;
+    size_t words;
+    int device;
+  };
+  static constexpr size_t kKeptWords = (size_t)1 << 19;  // 4 MB
+  static constexpr int kMostKept = 64;
+  inline static std::mutex mu;
+  inline static Kept kept[kMostKept];
+  inline static int n_kept = 0;
+
+  int reserve(size_t n, int dev, bool arena) {
+    device = dev;
+    in_arena = arena;
+    if (arena) {
+      std::lock_guard<std::mutex> g(mu);
+      for (int i = 0; i < n_kept; ++i)
+        if (kept[i].device == dev && kept[i].words >= n) {
+          p = kept[i].p;
+          words = kept[i].words;
+          kept[i] = kept[--n_kept];
+          return HD_OK;
+        }
+    }
+    if (hipHostMalloc((void**)&p, n * 8, hipHostMallocDefault) != hipSuccess) {
       p = nullptr;
       return fail(HD_ENOMEM, "pinned host memory for read-outs");
     }
+    words = n;
     return HD_OK;
   }
   ~HostBuf() {
-    if (p) (void)hipHostFree(p);
+    if (!p) return;
+    Kept out[kMostKept];
+    int n = 0;
+    {
+      std::lock_guard<std::mutex> g(mu);
+      if (in_arena) {
+        size_t held = words;
+        for (int i = 0; i < n_kept; ++i) held += kept[i].words;
+        if (held <= kKeptWords && n_kept < kMostKept) {
+          kept[n_kept++] = {p, words, device};
+          return;
+        }
+      }
+      std::copy(kept, kept + n_kept, out);
+      std::swap(n, n_kept);
+    }
+    (void)hipHostFree(p);
+    for (int i = 0; i < n; ++i) (void)hipHostFree(out[i].p);
   }
 };
 
@@ -957,7 +1006,7 @@ struct Batch : BatchBase {
     HD_TRY(upload_desc());
     size_t words = 0;
     for (const auto& h : hs) words = std::max(words, (size_t)readout_of(h).off[kRoParts]);
-    if (int rc = host.reserve(words)) return rc;
+    if (int rc = host.reserve(words, device, mem.arena != nullptr)) return rc;
     HD_TRY(launch_finalize<P>(d_desc, D, 1, nn_max, 0, stream));
     HD_TRY(hipStreamSynchronize(stream));
     for (int i = 0; i < D; ++i) {  // the field of step 0 must be finite
@@ -1861,7 +1910,8 @@ struct Server : ServerBase {
     HD_TRY(hipMalloc((void**)&d_idle, sizeof(State) * (size_t)S));
     HD_TRY(hipMemset(d_idle, 0, sizeof(State) * (size_t)S));
     HD_TRY(hipMalloc((void**)&d_desc, sizeof(Disch<P>) * S));
-    if (int rc = host.reserve(readout_layout((size_t)nn_max, 1, (size_t)nb1_max).off[kRoParts])) return rc;
+    if (int rc = host.reserve(readout_layout((size_t)nn_max, 1, (size_t)nb1_max).off[kRoParts], device, false))
+      return rc;
     hs.resize(S);
     slot_job.assign(S, nullptr);
     slot_done.assign(S, 0);
