@@ -469,7 +469,7 @@ __device__ __forceinline__ void solve_tridiag_block(int n, double* a, double* b,
     const int p = tid;
     const int s = p * n / P;
     const int e = (p + 1) * n / P - 1;
-    const int batches = (n / P - 4) / kSweep;  // of the n / P - 4 rows every lane sweeps
+    const int batches = (n / P - 3) / kSweep;  // of the n / P - 3 rows every lane sweeps
     // forward over the interior rows s+1 .. e-1
     double *pa = a + s + 1, *pb = b + s + 1, *pc = c + s + 1, *pd = d + s + 1;
     double rr = 1.0 / *pb;

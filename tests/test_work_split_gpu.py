@@ -77,3 +77,16 @@ def test_one_large_discharge_among_many(small, precision, groups):
         orc.step(19)
         compare(b.moments(i), b.particles(i), orc)
     b.close()
+
+
+@pytest.mark.parametrize("cells", [9, 17, 130, 257, 449, 450, 453, 705, 4096])
+def test_partitioned_solve_at_the_edges_of_its_batches(cells):
+    # partitions whose rows (less the three that start and end a sweep) are a
+    # multiple of the sweeps' batch, or one more or less
+    p = W.small(precision=1, ion_model=W.ION_FULL_FIT, n_cells=cells, gap_m=0.5e-3, n_macro=20000,
+                load_lo=0.0, load_hi=1.0)
+    dev, orc = hd.Discharge(p), oracle.Oracle(p, contract=True)
+    dev.step(5)
+    orc.step(5)
+    compare(dev.moments(), dev.particles(), orc)
+    dev.close()
