@@ -65,7 +65,7 @@ template <class P>
 hipError_t sort_set_lds(int nc_max, int D);
 size_t sort_lds_bytes(int nc_max, int D);
 template <class P>
-hipError_t launch_checkpoint(const Disch<P>* d_dev, int D, int restore, int grid, hipStream_t s);
+hipError_t launch_checkpoint(const Disch<P>* d, int restore, int grid, hipStream_t s);
 size_t sort_parts(size_t nc, size_t tiles);
 template <class P>
 hipError_t launch_set_steps(const Disch<P>* d_dev, int D, int64_t n, hipStream_t s);
@@ -1089,7 +1089,7 @@ struct Batch : BatchBase {
   // electrons, all close to capacity: 217 us per interval of 16 steps).
   hipError_t checkpoint() {
     if (D != 1) return hipSuccess;
-    return launch_checkpoint<P>(d_desc, D, 0, std::max(1, cus * 2), stream);
+    return launch_checkpoint<P>(d_desc, 0, std::max(1, cus * 2), stream);
   }
 
   // One step; at an interval's start (ckpt) the checkpoint launch first.
@@ -1204,7 +1204,7 @@ struct Batch : BatchBase {
   // handle then stands at the last complete step.
   int rollback(State& st) {
     const int64_t target = st.error_step;
-    HD_TRY(launch_checkpoint<P>(d_desc, D, 1, std::max(1, cus * 2), stream));
+    HD_TRY(launch_checkpoint<P>(d_desc, 1, std::max(1, cus * 2), stream));
     HD_TRY(hipStreamSynchronize(stream));
     HD_TRY(hipMemcpy(&st, hs[0].dd.st, sizeof(State), hipMemcpyDeviceToHost));
     host_step = st.step;

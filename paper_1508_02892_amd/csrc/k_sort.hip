@@ -516,8 +516,8 @@ __global__ void k_sort_finish(const Disch<P>* __restrict__ ds, int D) {
   st->prev_n_main = n;
 }
 
-// Checkpoint of a sort interval's start, for rolling back an interval whose
-// particles overflow the capacity.  restore = 0, at the interval's start:
+// Checkpoint of the start of a single discharge's sort interval, for rolling
+// back an interval whose particles overflow the capacity.  restore = 0, at the interval's start:
 // when the start was judged close to capacity (ckpt_due) the live slots
 // [0, n_main) go to the other particle buffer (unused until the interval's
 // sort, which an overflow suppresses) and the grid region and the State to
@@ -525,73 +525,53 @@ __global__ void k_sort_finish(const Disch<P>* __restrict__ ds, int D) {
 // restore = 1: everything is copied back (the State last, by one thread;
 // the copies read only the checkpoint).
 template <class P>
-__global__ __launch_bounds__(kThreads) void k_checkpoint(const Disch<P>* __restrict__ ds, int D,
+__global__ __launch_bounds__(kThreads) void k_checkpoint(const Disch<P>* __restrict__ dp,
                                                          int restore) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t gsz = (size_t)gridDim.x * blockDim.x;
-  // restore = 0: the decisions of kThreads discharges at a time are read in
-  // parallel (1: take a checkpoint, 2: mark it invalid, 0: keep it), so that
-  // a batch does not wait for one state's round trip per discharge
-  __shared__ uint8_t take[kThreads];
-  for (int g0 = 0; g0 < D; g0 += kThreads) {
-    const int ng = min(kThreads, D - g0);
+  const Disch<P>& d = *dp;
+  State* st = d.st;
+  State* sv = reinterpret_cast<State*>(d.ckpt + d.grid_bytes);
+  if (restore) {
+    if (!st->ckpt_valid) return;
+  } else {
+    if (st->error) return;  // an interval stopped by an error keeps its checkpoint
+    if (!st->ckpt_due || st->steps_left <= 0) {
+      if (gid == 0) st->ckpt_valid = 0;
+      return;
+    }
+  }
+  const int cur = restore ? sv->buf : st->buf;
+  const size_t n = restore ? sv->n_main : st->n_main;
+  const int src = restore ? cur ^ 1 : cur, dst = src ^ 1;
+  for (size_t i = gid; i < n; i += gsz) {
+    d.cell[dst][i] = d.cell[src][i];
+    d.off[dst][i] = d.off[src][i];
+    d.vx[dst][i] = d.vx[src][i];
+    d.vy[dst][i] = d.vy[src][i];
+    d.vz[dst][i] = d.vz[src][i];
+    d.id[dst][i] = d.id[src][i];
+  }
+  uint4* grid = reinterpret_cast<uint4*>(d.cnt[0]);
+  uint4* keep = reinterpret_cast<uint4*>(d.ckpt);
+  const size_t words = d.grid_bytes / 16;
+  for (size_t w = gid; w < words; w += gsz) {
+    if (restore)
+      grid[w] = keep[w];
+    else
+      keep[w] = grid[w];
+  }
+  if (gid == 0) {
     if (!restore) {
-      uint8_t f = 0;
-      if ((int)threadIdx.x < ng) {
-        State* st = ds[g0 + (int)threadIdx.x].st;
-        const int err = st->error;
-        const int due = st->ckpt_due;
-        const int64_t left = st->steps_left;
-        // an interval stopped by an error keeps its checkpoint
-        f = err ? 0 : ((due && left > 0) ? 1 : 2);
-        if (f == 2 && blockIdx.x == 0) st->ckpt_valid = 0;
-      }
-      take[threadIdx.x] = f;
-      __syncthreads();
+      *sv = *st;
+      st->ckpt_valid = 1;
+      st->ckpt_step = st->step;
+    } else {
+      State x = *sv;
+      x.ckpt_valid = 1;  // the checkpoint still holds this state
+      x.ckpt_step = x.step;
+      *st = x;
     }
-    for (int di = g0; di < g0 + ng; ++di) {
-      const Disch<P>& d = ds[di];
-      State* st = d.st;
-      State* sv = reinterpret_cast<State*>(d.ckpt + d.grid_bytes);
-      if (!restore) {
-        if (take[di - g0] != 1) continue;
-      } else if (!st->ckpt_valid) {
-        continue;
-      }
-      const int cur = restore ? sv->buf : st->buf;
-      const size_t n = restore ? sv->n_main : st->n_main;
-      const int src = restore ? cur ^ 1 : cur, dst = src ^ 1;
-      for (size_t i = gid; i < n; i += gsz) {
-        d.cell[dst][i] = d.cell[src][i];
-        d.off[dst][i] = d.off[src][i];
-        d.vx[dst][i] = d.vx[src][i];
-        d.vy[dst][i] = d.vy[src][i];
-        d.vz[dst][i] = d.vz[src][i];
-        d.id[dst][i] = d.id[src][i];
-      }
-      uint4* grid = reinterpret_cast<uint4*>(d.cnt[0]);
-      uint4* keep = reinterpret_cast<uint4*>(d.ckpt);
-      const size_t words = d.grid_bytes / 16;
-      for (size_t w = gid; w < words; w += gsz) {
-        if (restore)
-          grid[w] = keep[w];
-        else
-          keep[w] = grid[w];
-      }
-      if (gid == 0) {
-        if (!restore) {
-          *sv = *st;
-          st->ckpt_valid = 1;
-          st->ckpt_step = st->step;
-        } else {
-          State x = *sv;
-          x.ckpt_valid = 1;  // the checkpoint still holds this state
-          x.ckpt_step = x.step;
-          *st = x;
-        }
-      }
-    }
-    if (!restore) __syncthreads();  // take[] is refilled for the next discharges
   }
 }
 
@@ -624,8 +604,8 @@ hipError_t launch_sort_impl(const Disch<P>* d_dev, int D, int grid, int tile, in
 }
 
 template <class P>
-hipError_t launch_checkpoint(const Disch<P>* d_dev, int D, int restore, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_checkpoint<P>, dim3(grid), dim3(kThreads), 0, s, d_dev, D, restore);
+hipError_t launch_checkpoint(const Disch<P>* d, int restore, int grid, hipStream_t s) {
+  hipLaunchKernelGGL(k_checkpoint<P>, dim3(grid), dim3(kThreads), 0, s, d, restore);
   return hipGetLastError();
 }
 
@@ -663,8 +643,8 @@ size_t sort_lds_bytes(int nc_max, int D) {
 size_t sort_parts(size_t nc, size_t tiles) { return (nc * tiles + kScanBlock - 1) / kScanBlock + 1; }
 
 template hipError_t launch_sort_impl<float>(const Disch<float>*, int, int, int, int, hipStream_t);
-template hipError_t launch_checkpoint<float>(const Disch<float>*, int, int, int, hipStream_t);
-template hipError_t launch_checkpoint<double>(const Disch<double>*, int, int, int, hipStream_t);
+template hipError_t launch_checkpoint<float>(const Disch<float>*, int, int, hipStream_t);
+template hipError_t launch_checkpoint<double>(const Disch<double>*, int, int, hipStream_t);
 template hipError_t launch_sort_impl<double>(const Disch<double>*, int, int, int, int,
                                             hipStream_t);
 template hipError_t sort_set_lds<float>(int, int);
