@@ -47,6 +47,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ["paper_1508_02892_amd/csrc/k_electron.h",
                   "paper_1508_02892_amd/csrc/k_electron_full.hip",
+                  "paper_1508_02892_amd/csrc/work_split.h",
                   "paper_1508_02892_amd/csrc/hd_device.h",
                   "paper_1508_02892_amd/csrc/hd_internal.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_electron_c1_traffic.md")

@@ -358,8 +358,10 @@ typedef struct hd_launch_config {
                                four waves per SIMD where large grids leave
                                LDS for only one narrow workgroup (the
                                autotuner also tries them when the particle
-                               state exceeds the MALL); FP32 only, and not
-                               for variant 1 (9 is rejected)               */
+                               state exceeds the MALL); built for FP32 only
+                               (FP64 collision queues of sixteen waves take
+                               96 KB of the LDS), and not for variant 1 (9 is
+                               rejected)                                   */
   int32_t electron_groups;  /* workgroups that the electron launch divides
                                its work for, 1 .. 4096 (0: as many as fit on
                                the device at once); a batch of more than an

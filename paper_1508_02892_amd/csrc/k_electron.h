@@ -4,8 +4,8 @@
 //
 // Each active discharge's sub-chunks (256 slots, one wave's work at a time)
 // and, counted as some sub-chunks more, its ion fluid are split into
-// contiguous ranges of equal length, one per workgroup, whose waves take the
-// sub-chunks of the range in turn.  A workgroup keeps the collision table, a
+// contiguous ranges of equal length (work_split.h), one per workgroup, whose
+// waves take the sub-chunks of the range in turn.  A workgroup keeps the collision table, a
 // fixed-point deposit grid, the EEDF histogram and event counters of its
 // discharge in LDS and flushes them once.  Collisions are compacted into an
 // LDS queue by a ballot prefix sum, so that the rare scattering work runs on
@@ -24,10 +24,11 @@
 // The kernels are compiled once per kind of batch (HD_ELEC_KIND, set by the
 // source that includes this file): the code of the ion fluids and of the
 // general channel loop that a batch cannot need then takes no registers, and
-// no instruction cache, from its particle loop (all in one kernel: 297
-// scalars spilled to vector lanes and 119 VGPRs, by itself 129 and 94; the
-// launch of 24 discharges with 2^24 electrons 123.3 to 119.2 us, of 64 small
-// ones 24.2 to 22.8, of 17.8 M electrons on 4,096 cells 123.8 to 120.2).
+// no instruction cache, from its particle loop (three channels in the kernels
+// of any batch: 94 scalars spilled to vector lanes and 74 VGPRs, in their own 43
+// and 71; when the split into kinds was made, the launch of 24 discharges with
+// 2^24 electrons went from 123.3 to 119.2 us, of 64 small ones from 24.2 to
+// 22.8, of 17.8 M electrons on 4,096 cells from 123.8 to 120.2).
 #pragma once
 
 #include <type_traits>
@@ -1267,9 +1268,10 @@ __device__ __forceinline__ void fluid_update(const Disch<P>& d, double* lds, uin
 }
 
 // An ion-fluid update in sub-chunks of particle work: what a workgroup could
-// do of those in its time, at 0.6 to 0.8 us per sub-chunk (the full fluid 29 us
-// at 2,047 rows and 38 beside the particles of a full launch, drift-diffusion 2
-// to 6 us).
+// do of those in its time, at 0.8 us per sub-chunk with two FP32 workgroups per
+// CU and 0.6 with one FP64 workgroup (the full fluid 29 us at 2,047 rows and 38
+// beside the particles of a full launch, drift-diffusion 2 to 6 us, four species
+// about 5 at 1,025 nodes).
 template <class P>
 __device__ __forceinline__ uint32_t fluid_subs(const Disch<P>& d) {
   const bool full = d.ion_model == HD_ION_FULL_CONST_NU || d.ion_model == HD_ION_FULL_FIT_NU;
@@ -1416,13 +1418,12 @@ __device__ __forceinline__ void electron_body(const Disch<P>* __restrict__ ds, c
   if (u0 < u1) segment<P, M, W, Q>(d, u0, u1, smem, L, r, per);
 }
 
-// FP32: at most 128 VGPRs so that four waves share each SIMD, and no more
-// waves, for which the compiler would save registers at the price of waits
-// (on 4,096 cells, where one wide workgroup has a CU, 161 us per step of 17.8 M
-// electrons instead of 159.7).  Each kernel
-// but the register-prefetch one has a wide twin (suffix _w): the same body
-// with 1,024-thread workgroups, one per CU, for grids whose LDS leaves room
-// for only one narrow workgroup per CU.
+// FP32: at most 128 VGPRs so that four waves share each SIMD, and compiled for
+// no more, for which registers would be saved at the price of waits (17.8 M
+// electrons on 4,096 cells, where one wide workgroup has a CU: 161 us per step
+// instead of 159.7).  Each kernel but the register-prefetch one has a wide twin
+// (suffix _w): the same body with 1,024-thread workgroups, one per CU, for grids
+// whose LDS leaves room for only one narrow workgroup per CU.
 template <int M, int W>
 __device__ __forceinline__ void f32_body(const Disch<float>* __restrict__ ds, const ElecArgs& a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1452,8 +1453,8 @@ HD_F32_KERNEL(k_electron_f32_nd_np, 6)
 HD_F32_KERNEL(k_electron_f32_nt_sw, 28)
 #undef HD_F32_KERNEL
 
-// FP32 with the next chunk's loads in flight: at most 168 VGPRs, three
-// waves per SIMD.
+// FP32 with the next chunk's loads in flight: compiled for three waves per SIMD
+// (at most 168 VGPRs; it takes 96 to 102).
 __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(3))) void
 k_electron_f32_pf(const Disch<float>* __restrict__ ds, ElecArgs a) {
   f32_body<1, 8>(ds, a);

@@ -18,9 +18,12 @@ static const void* elec_kernel_of(int kind, bool f64, int variant) {
 }
 
 // Variant v < kElecWide: kernel v with kElecThreads per workgroup;
-// kElecWide + v: its wide twin with kElecThreadsWide (FP32 only: the FP64
-// kernels and the register-prefetch kernel use more registers than sixteen
-// waves per CU allow, so they have none and those variants are rejected).
+// kElecWide + v: its wide twin with kElecThreadsWide.  The FP64 kernels and the
+// register-prefetch kernel have none and those variants are rejected: in FP64
+// sixteen waves' collision queues take 96 KB, which leaves no room for the
+// arrays of the large grids that wide workgroups are for, and the prefetch
+// kernel is for few waves.  Registers would allow most of them (97 to 102 VGPRs
+// of 128; 141 to 144 for FP64 with the prefetch).
 inline int elec_threads(int variant) {
   return variant >= kElecWide ? kElecThreadsWide : kElecThreads;
 }
