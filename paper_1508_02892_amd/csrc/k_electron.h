@@ -1429,28 +1429,31 @@ __device__ __forceinline__ void f32_body(const Disch<float>* __restrict__ ds, co
   extern __shared__ __align__(16) unsigned char smem[];
   electron_body<float, M, W, HD_ELEC_KIND>(ds, a, smem);
 }
-#define HD_F32_KERNEL(NAME, M)                                                                \
-  __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void     \
-  NAME(const Disch<float>* __restrict__ ds, ElecArgs a) {                                    \
-    f32_body<M, 8>(ds, a);                                                                   \
-  }                                                                                          \
-  __global__ __launch_bounds__(kElecThreadsWide) __attribute__((amdgpu_waves_per_eu(4, 4))) void \
-  NAME##_w(const Disch<float>* __restrict__ ds, ElecArgs a) {                                \
-    f32_body<M, 16>(ds, a);                                                                  \
+#define HD_F32_KERNEL(NAME, M, ...)                                                           \
+  __global__ __launch_bounds__(kElecThreads) __attribute__((amdgpu_waves_per_eu(__VA_ARGS__))) \
+  void NAME(const Disch<float>* __restrict__ ds, ElecArgs a) {                                \
+    f32_body<M, 8>(ds, a);                                                                    \
+  }                                                                                           \
+  __global__ __launch_bounds__(kElecThreadsWide)                                              \
+  __attribute__((amdgpu_waves_per_eu(__VA_ARGS__)))                                           \
+  void NAME##_w(const Disch<float>* __restrict__ ds, ElecArgs a) {                            \
+    f32_body<M, 16>(ds, a);                                                                   \
   }
-HD_F32_KERNEL(k_electron_f32, 0)
+HD_F32_KERNEL(k_electron_f32, 0, 4, 4)
 // loads issued without draining the stores first
-HD_F32_KERNEL(k_electron_f32_nd, 2)
+HD_F32_KERNEL(k_electron_f32_nd, 2, 4, 4)
 // nontemporal particle loads and write-backs (for particle stores far beyond
 // the MALL), with and without the drain; then the same with the velocities
 // left to the caches
-HD_F32_KERNEL(k_electron_f32_nt, 12)
-HD_F32_KERNEL(k_electron_f32_nd_nt, 14)
-HD_F32_KERNEL(k_electron_f32_np, 4)
-HD_F32_KERNEL(k_electron_f32_nd_np, 6)
+HD_F32_KERNEL(k_electron_f32_nt, 12, 4, 4)
+HD_F32_KERNEL(k_electron_f32_nd_nt, 14, 4, 4)
+HD_F32_KERNEL(k_electron_f32_np, 4, 4, 4)
+HD_F32_KERNEL(k_electron_f32_nd_np, 6, 4, 4)
 // all particle traffic nontemporal and each chunk's collisions handled
-// before its velocities are written (whole segments only)
-HD_F32_KERNEL(k_electron_f32_nt_sw, 28)
+// before its velocities are written (whole segments only); the most live
+// registers, and the one that is faster when they are kept few (64
+// discharges with 2^26 electrons, wide: 635 us per step instead of 643)
+HD_F32_KERNEL(k_electron_f32_nt_sw, 28, 4)
 #undef HD_F32_KERNEL
 
 // FP32 with the next chunk's loads in flight: compiled for three waves per SIMD
